@@ -888,6 +888,397 @@ __global__ __launch_bounds__(64 * NW, 1) void sparse_mla_mfma(
         }
 }
 
+// MLA with 16, 32 or 64 heads (bf16 rows): the heads of one tensor-parallel
+// shard.  Every row still gathers its whole selection, so the gather bounds
+// the kernel: 4.8 GB at 2048 rows x 2048 ids.  The kernel above, whose ring of
+// 32-key tiles fills the CU's LDS, would run one wave per 16 heads through
+// each tile's chain of phases: one to four waves per CU.  Here HB head blocks
+// x NG key groups run as HB * NG waves: wave (hb, group) holds the queries of
+// head block hb, takes the 16-key tiles T = group, group + NG, ... and keeps
+// its own softmax state and all 512 output dims (128 registers), so that no P
+// is exchanged and only the hand-over of a tile shared by a group's waves
+// needs a barrier (none with one head block).  The groups are merged once per
+// row, through LDS.  A group's ring has RING tiles of 18 KB; NG * RING = 8
+// tiles and the slots fill the 160 KB.  P V runs on the 16-key MFMA at half
+// its 32-key rate: MFMA time is not what bounds these head counts, and a
+// 32-key tile would halve the groups.  Measured at 2048 rows x 2048 ids of a
+// 64K history: 16 heads 1793 -> 448 us (10.8 TB/s of logical gather), 32
+// heads 1323 -> 497, 64 heads 1158 -> 864.  With 128 heads the waves' own
+// reads of V (each all of it) would bound the kernel; the kernel above shares
+// them.
+//
+// Tile layout: dims 0..511 of row r (1 KB) at 1024 r, 16-byte chunk c at slot
+// c ^ few_swz(r): the 16 rows of a K operand read fall in 16 different
+// 16-byte bank groups, and the 8 rows x 32 bytes of half a transposing V read
+// too.  Dims 512..575 follow in two 1 KB blocks of eight rows, laid out as
+// the kernel above lays out its tail blocks.
+constexpr int FEW_KT = 16;
+constexpr int FEW_TAIL = FEW_KT * 1024;
+constexpr int FEW_TILEB = FEW_TAIL + 2 * 1024;
+constexpr int FEW_TILES = 8;       // tile buffers per block
+constexpr int FEW_DIMS = 128;      // output dims per merge round
+constexpr int FEW_PITCH = FEW_DIMS + 4;  // floats per head in a merge round (the four lane groups' rows in distinct banks)
+template <int HB>
+constexpr int few_groups() { return HB == 4 ? 2 : 4; }
+JANUS_DEV int few_swz(int r) { return ((r << 1) & 15) | (r >> 3); }
+JANUS_DEV int few_tail(int r, int cc)
+{
+    const int m = r >> 3;
+    return FEW_TAIL + 1024 * m + 16 * (8 * (cc ^ m) + ((r & 7) ^ cc));
+}
+
+// 16 bytes per lane from a wave-uniform row (byte offset off per lane) into
+// LDS at dst + 16 l: gather16 with the row's address in scalar registers.
+JANUS_DEV void gather16_row(const uint8_t *row, uint32_t off, uint32_t lds)
+{
+    int saved;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3\n\t"
+                 "s_mov_b32 m0, %0"
+                 : "=&s"(saved)
+                 : "s"(lds), "v"(off), "s"(row)
+                 : "memory");
+}
+
+// (bounds of 512 threads also for the 256 of one head block: at one wave per
+// SIMD the compiler moves O to AGPRs and copies it out and back on every tile)
+template <int HB, bool SPLIT>
+__global__ __launch_bounds__(512, 2) void sparse_mla_few(
+    const int32_t *__restrict__ q_start, const int32_t *__restrict__ hist_len, int num_seqs, int es,
+    const uint16_t *__restrict__ q, const uint8_t *__restrict__ kv, int64_t row_bytes,
+    const int32_t *__restrict__ page_table, int pt_ld, int page_shift, const int32_t *__restrict__ topk,
+    int k, float scale_log2, void *__restrict__ out, int out_f32, float *__restrict__ lse, int num_splits,
+    float *__restrict__ part)
+{
+    constexpr int NG = few_groups<HB>(), RING = FEW_TILES / NG, NW = HB * NG, NT = 64 * NW, HQ = 16 * HB;
+    constexpr int ROWS = FEW_KT / HB;          // main rows a wave gathers per tile
+    constexpr int NTAIL = HB == 1 ? 2 : 1;     // tail blocks (waves hb < 2)
+    __shared__ __attribute__((aligned(16))) uint8_t sTile[FEW_TILES * FEW_TILEB];
+    __shared__ int32_t sSlot[MLA_MAX_K];
+    const int g = SPLIT ? blockIdx.x / num_splits : blockIdx.x;
+    int kl = k;
+    const int32_t *sel = topk + (int64_t)g * k;
+    if constexpr (SPLIT) {
+        const int sp = blockIdx.x % num_splits;
+        const int tps = ((k + MLA_KT - 1) / MLA_KT + num_splits - 1) / num_splits;
+        const int j0 = min(k, sp * tps * MLA_KT);
+        kl = min(k, j0 + tps * MLA_KT) - j0;
+        sel += j0;
+    }
+    const int b = session_of_row(q_start, num_seqs, g);
+    const int lim = last_cand(hist_len[b], g - q_start[b], es);
+    const int32_t *pt = page_table + (int64_t)b * pt_ld;
+    const int psz_mask = (1 << page_shift) - 1;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int hb = wave % HB, grp_k = wave / HB;  // head block, key group
+    const int c16 = lane & 15, grp = lane >> 4;
+    for (int j = tid; j < kl; j += NT) {
+        const int s = sel[j];
+        sSlot[j] = (s >= 0 && s <= lim) ? ((pt[s >> page_shift] << page_shift) + (s & psz_mask)) : -1;
+    }
+    // queries of head 16*hb + c16, dims 32*st + 8*grp .. +7
+    v8bf qf[MLA_STEPS];
+    {
+        const uint16_t *qr = q + ((int64_t)g * HQ + 16 * hb + c16) * MLA_DQK + 8 * grp;
+#pragma unroll
+        for (int st = 0; st < MLA_STEPS; ++st)
+            qf[st] = as_v8bf(*(const v4i *)(qr + 32 * st));
+    }
+    // O for heads 4*grp + i of the block over dims 16*nb + c16
+    v4f o[MLA_NB];
+#pragma unroll
+    for (int nb = 0; nb < MLA_NB; ++nb)
+        o[nb] = v4f{0.f, 0.f, 0.f, 0.f};
+    float m = M_INIT, lsum = 0.f;  // head c16 of the block
+    const int ntiles = (kl + FEW_KT - 1) / FEW_KT;
+    const int nsteps = (ntiles + NG - 1) / NG;
+    uint8_t *ring = sTile + grp_k * RING * FEW_TILEB;
+
+    // this wave's share of the gather of its group's tile at step s (a tile
+    // past the selection gathers row 0, so that the counts stay fixed)
+    const uint32_t rb = (uint32_t)row_bytes;
+    const uint32_t ring_lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void *)ring);
+    // an opaque copy of the lane index: what is derived from it is made
+    // where it is used, not kept in registers across the loop
+    auto lane_copy = [&]() {
+        int ln = lane;
+        asm volatile("" : "+v"(ln));
+        return ln;
+    };
+    struct Slots {
+        int main, tail[NTAIL];
+    };
+    // slots of step s: lane l holds row l % 16's, and tail[u] the one of the
+    // row that this lane loads in a tail block: lane l fills slot
+    // l = 8*(cc ^ mb) + (i ^ cc) of block mb with chunk cc of row 8*mb + i
+    auto read_slots = [&](int s, Slots &v) {
+        const int k0 = FEW_KT * (s * NG + grp_k), ln = lane_copy();
+        int x = sSlot[min(k0 + (ln & 15), kl - 1)];
+        v.main = k0 + (ln & 15) < kl ? max(x, 0) : 0;  // padding rows read a real row; their logits are masked
+#pragma unroll
+        for (int u = 0; u < NTAIL; ++u) {
+            const int mb = HB == 1 ? u : (hb & 1), cc = (ln >> 3) ^ mb, r = 8 * mb + ((ln & 7) ^ cc);
+            x = sSlot[min(k0 + r, kl - 1)];
+            v.tail[u] = k0 + r < kl ? max(x, 0) : 0;
+        }
+    };
+    auto fire_main = [&](int s, int i, const Slots &v) {
+        const int r = ROWS * hb + i;
+        const uint32_t sl = (uint32_t)__builtin_amdgcn_readlane(v.main, r);
+        gather16_row(kv + (uint64_t)sl * rb, (16u * lane_copy()) ^ (16u * few_swz(r)),
+                     ring_lds + (uint32_t)((s % RING) * FEW_TILEB + 1024 * r));
+    };
+    auto fire_tail = [&](int s, int u, const Slots &v) {
+        if (HB > 2 && hb >= 2)
+            return;
+        const int mb = HB == 1 ? u : (hb & 1), cc = (lane_copy() >> 3) ^ mb;
+        gather16(kv + (uint64_t)(uint32_t)v.tail[u] * rb + 16 * (64 + cc),
+                 ring + (s % RING) * FEW_TILEB + FEW_TAIL + 1024 * mb);
+    };
+    auto issue = [&](int s) {
+        Slots v;
+        read_slots(s, v);
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i)
+            fire_main(s, i, v);
+#pragma unroll
+        for (int u = 0; u < NTAIL; ++u)
+            fire_tail(s, u, v);
+    };
+    // this wave's gathers have landed up to those of the newest `pend` steps
+    auto wait_steps = [&](int pend) {
+        constexpr int IPW = ROWS + NTAIL;
+        const bool tail = HB <= 2 || hb < 2;
+        if (pend <= 0)
+            __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
+        else if (pend == 1)
+            tail ? __builtin_amdgcn_s_waitcnt(vmcnt_only(IPW)) : __builtin_amdgcn_s_waitcnt(vmcnt_only(ROWS));
+        else
+            tail ? __builtin_amdgcn_s_waitcnt(vmcnt_only(2 * IPW)) : __builtin_amdgcn_s_waitcnt(vmcnt_only(2 * ROWS));
+    };
+    // K operands in flight ahead of their MFMA, and V operands read before
+    // the softmax (one wave per SIMD has the registers for all of K)
+    constexpr int KAHEAD = 4, VAHEAD = 8;
+    // computes step s; with NEXT, step s + RING - 1's gathers go out among its MFMAs
+    auto compute = [&](int s, auto nextc) {
+        constexpr bool NEXT = decltype(nextc)::value;
+        const int k0 = FEW_KT * (s * NG + grp_k), sn = s + RING - 1;
+        const uint8_t *tile = ring + (s % RING) * FEW_TILEB;
+        Slots nv;
+        if constexpr (NEXT)
+            read_slots(sn, nv);
+        const int ln = lane_copy(), lc = ln & 15, lg = ln >> 4;
+        const int vslot = sSlot[min(k0 + lc, kl - 1)];
+        // K operand of K-step st: row lc, chunk 4*st + lg; V operand of dims
+        // 16*nb ..: row 4*lg + lc/4, dims 16*nb + 4*(lc%4) ..  Both walk the
+        // swizzled chunks so that one address serves four reads: the n-th
+        // K-step is st = 4*(n%4) + n/4, the n-th V block nb = 8*(n%4) + n/4
+        const int kaddr = 1024 * lc + 16 * (lg ^ few_swz(lc));
+        auto kop = [&](int n) {
+            const int off = n < 16 ? (kaddr ^ (64 * (n >> 2))) + 256 * (n & 3) : few_tail(lc, 4 * (n - 16) + lg);
+            return as_v8bf(*(const v4i *)(tile + off));
+        };
+        const int vr0 = 4 * lg + (lc >> 2);
+        const int vaddr = 1024 * vr0 + 16 * (((lc >> 1) & 1) ^ few_swz(vr0)) + 8 * (lc & 1);
+        auto vop = [&](int n) { return lds_read_tr16(tile, (vaddr ^ (32 * (n >> 2))) + 256 * (n & 3)); };
+        // S^T[key 4*grp + i][head c16] in two chains
+        v4f s0 = v4f{0.f, 0.f, 0.f, 0.f}, s1 = s0;
+        v8bf kr[KAHEAD];
+#pragma unroll
+        for (int n = 0; n < KAHEAD; ++n)
+            kr[n] = kop(n);
+#pragma unroll
+        for (int n = 0; n < MLA_STEPS; ++n) {
+            const int st = n < 16 ? 4 * (n & 3) + (n >> 2) : n;
+            if (n & 1)
+                s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kr[n % KAHEAD], qf[st], s1, 0, 0, 0);
+            else
+                s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kr[n % KAHEAD], qf[st], s0, 0, 0, 0);
+            if (n + KAHEAD < MLA_STEPS)
+                kr[n % KAHEAD] = kop(n + KAHEAD);
+            if constexpr (NEXT) {
+                // ROWS main gathers from the second K-step on, the tails at the end
+                if (n >= 1 && n <= 16 && (n - 1) % HB == 0)
+                    fire_main(sn, (n - 1) / HB, nv);
+                if (n == 17)
+#pragma unroll
+                    for (int u = 0; u < NTAIL; ++u)
+                        fire_tail(sn, u, nv);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        v4s16 vr[VAHEAD];
+#pragma unroll
+        for (int n = 0; n < VAHEAD; ++n)
+            vr[n] = vop(n);
+        const uint32_t vmask = (uint32_t)__ballot(k0 + lc < kl && vslot >= 0) >> (4 * lg);
+        float x[4], mx = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            x[i] = ((vmask >> i) & 1u) ? (s0[i] + s1[i]) * scale_log2 : -INFINITY;
+            mx = fmaxf(mx, x[i]);
+        }
+        // the running max moves (for all four lane groups of a head) only when a logit exceeds it by the slack
+        if (__ballot(mx > m + RESCALE_SLACK) != 0) {
+            const int lr = lane_here();
+            auto from = [&](int l, float v) {
+                return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute(l << 2, __builtin_bit_cast(int, v)));
+            };
+            mx = fmaxf(mx, from(lr ^ 16, mx));
+            mx = fmaxf(mx, from(lr ^ 32, mx));
+            const float mnew = mx > m + RESCALE_SLACK ? mx : m;
+            const float alpha = __builtin_amdgcn_exp2f(m - mnew);
+            lsum *= alpha;
+            m = mnew;
+            float ai[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                ai[i] = from(4 * (lr >> 4) + i, alpha);
+#pragma unroll
+            for (int nb = 0; nb < MLA_NB; ++nb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    o[nb][i] *= ai[i];
+        }
+        float p[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            p[i] = __builtin_amdgcn_exp2f(x[i] - m);
+            lsum += p[i];
+        }
+        typedef __bf16 v4bf __attribute__((ext_vector_type(4)));
+        const v4s16 pa = __builtin_bit_cast(v4s16, (v4bf{(__bf16)p[0], (__bf16)p[1], (__bf16)p[2], (__bf16)p[3]}));
+#pragma unroll
+        for (int n = 0; n < MLA_NB; ++n) {
+            const int nb = 8 * (n & 3) + (n >> 2);
+            o[nb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pa, vr[n % VAHEAD], o[nb], 0, 0, 0);
+            if (n + VAHEAD < MLA_NB)
+                vr[n % VAHEAD] = vop(n + VAHEAD);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+
+    // the queries have landed before any gather goes out (the compiler does
+    // not count the gathers), and every slot is written
+    __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < RING - 1; ++s)
+        if (s < nsteps)
+            issue(s);
+    // step s's tile is whole, and the tile before it has been read by all of
+    // the group's waves (one wave: by itself)
+    auto arrive = [&](int s) {
+        wait_steps(min(RING - 2, nsteps - 1 - s));
+        if constexpr (HB > 1) {
+            lds_barrier();
+        } else {
+            __builtin_amdgcn_s_waitcnt(0xC07F);
+            asm volatile("" ::: "memory");
+        }
+    };
+    int s = 0;
+    for (; s + RING - 1 < nsteps; ++s) {
+        arrive(s);
+        compute(s, std::true_type{});
+    }
+    // the last steps have nothing left to gather, and at the very last one
+    // the last groups may have no tile
+    const int own = ntiles > grp_k ? (ntiles - grp_k + NG - 1) / NG : 0;
+    for (; s < own; ++s) {
+        arrive(s);
+        compute(s, std::false_type{});
+    }
+    if (s < nsteps)
+        arrive(s);
+
+    // merge of the key groups: each group's O scaled to the head's common max,
+    // summed in FEW_DIMS-wide rounds through LDS (over the tiles and slots)
+    lsum += __shfl_xor(lsum, 16, 64);
+    lsum += __shfl_xor(lsum, 32, 64);
+    __syncthreads();
+    float *sM = (float *)sSlot, *sL = sM + 16 * NW, *sInv = sL + 16 * NW, *sO = (float *)sTile;
+    if (grp == 0) {
+        sM[16 * wave + c16] = m;
+        sL[16 * wave + c16] = lsum;
+    }
+    __syncthreads();
+    float f[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int h = 4 * grp + i;
+        float mg = sM[16 * hb + h];
+#pragma unroll
+        for (int gk = 1; gk < NG; ++gk)
+            mg = fmaxf(mg, sM[16 * (gk * HB + hb) + h]);
+        f[i] = __builtin_amdgcn_exp2f(sM[16 * wave + h] - mg);
+    }
+    if (tid < HQ) {  // head tid: 16*(tid/16) + tid%16
+        float mg = sM[tid], l = 0.f;
+#pragma unroll
+        for (int gk = 1; gk < NG; ++gk)
+            mg = fmaxf(mg, sM[16 * HB * gk + tid]);
+#pragma unroll
+        for (int gk = 0; gk < NG; ++gk)
+            l += __builtin_amdgcn_exp2f(sM[16 * HB * gk + tid] - mg) * sL[16 * HB * gk + tid];
+        if constexpr (SPLIT) {
+            sInv[tid] = 1.f;  // the slices' merge normalises
+            float *ml = part + (int64_t)gridDim.x * HQ * MLA_DV + ((int64_t)blockIdx.x * HQ + tid) * 2;
+            ml[0] = l > 0.f ? mg : -INFINITY;
+            ml[1] = l;
+        } else {
+            sInv[tid] = l > 0.f ? 1.f / l : 0.f;
+            if (lse)
+                lse[(int64_t)g * HQ + tid] = l > 0.f ? (mg + log2f(l)) * LN2 : -INFINITY;
+        }
+    }
+    const bool wide = (reinterpret_cast<uintptr_t>(out) & 15) == 0;
+#pragma unroll
+    for (int r = 0; r < MLA_DV / FEW_DIMS; ++r) {
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < FEW_DIMS / 16; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                sO[(16 * wave + 4 * grp + i) * FEW_PITCH + 16 * j + c16] = o[r * (FEW_DIMS / 16) + j][i] * f[i];
+        __syncthreads();
+        for (int e = tid; e < HQ * (FEW_DIMS / 4); e += NT) {
+            const int h = e / (FEW_DIMS / 4), d4 = e % (FEW_DIMS / 4);
+            v4f a = *(const v4f *)(sO + h * FEW_PITCH + 4 * d4);
+#pragma unroll
+            for (int gk = 1; gk < NG; ++gk)
+                a += *(const v4f *)(sO + (HQ * gk + h) * FEW_PITCH + 4 * d4);
+            a *= sInv[h];
+            const int d = FEW_DIMS * r + 4 * d4;
+            if constexpr (SPLIT) {
+                *(v4f *)(part + ((int64_t)blockIdx.x * HQ + h) * MLA_DV + d) = a;
+            } else {
+                const int64_t at = ((int64_t)g * HQ + h) * MLA_DV + d;
+                if (out_f32) {
+                    float *dst = (float *)out + at;
+                    if (wide)
+                        *(v4f *)dst = a;
+                    else
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            dst[i] = a[i];
+                } else {
+                    uint16_t *dst = (uint16_t *)out + at;
+                    const uint16_t h0 = f32_to_bf16_rne(a[0]), h1 = f32_to_bf16_rne(a[1]), h2 = f32_to_bf16_rne(a[2]),
+                                   h3 = f32_to_bf16_rne(a[3]);
+                    if (wide) {
+                        *(v2i *)dst = v2i{(int)(h0 | ((uint32_t)h1 << 16)), (int)(h2 | ((uint32_t)h3 << 16))};
+                    } else {
+                        dst[0] = h0;
+                        dst[1] = h1;
+                        dst[2] = h2;
+                        dst[3] = h3;
+                    }
+                }
+            }
+        }
+    }
+}
+
 // MQA kernel for up to 16 query heads with dqk = dv = 128 and separate K and
 // V pools (the attention of the small config: 8 heads sharing one KV head).
 // One wave per query token, four independent waves per block (no block
@@ -1285,25 +1676,30 @@ static void launch_mla(const janus_batch *bt, const void *q, int Hq, const void 
                            bt->num_seqs, bt->entry_shift, qq, kv, row_bytes, page_table, pt_ld, shift, topk_idx, k,
                            sl2, out, of32, lse, splits, part);
     };
-    if (part) {
+    auto heads = [&](auto split) {
+        constexpr bool S = decltype(split)::value;
         if (Hq == 128)
-            launch(sparse_mla_mfma<8, true, KV8>, 8);
-        else if (Hq == 64)
-            launch(sparse_mla_mfma<4, true, KV8>, 4);
-        else if (Hq == 32)
-            launch(sparse_mla_mfma<2, true, KV8>, 2);
-        else
-            launch(sparse_mla_mfma<1, true, KV8>, 1);
-    } else {
-        if (Hq == 128)
-            launch(sparse_mla_mfma<8, false, KV8>, 8);
-        else if (Hq == 64)
-            launch(sparse_mla_mfma<4, false, KV8>, 4);
-        else if (Hq == 32)
-            launch(sparse_mla_mfma<2, false, KV8>, 2);
-        else
-            launch(sparse_mla_mfma<1, false, KV8>, 1);
-    }
+            launch(sparse_mla_mfma<8, S, KV8>, 8);
+        else if constexpr (!KV8) {
+            if (Hq == 64)
+                launch(sparse_mla_few<4, S>, 4 * few_groups<4>());
+            else if (Hq == 32)
+                launch(sparse_mla_few<2, S>, 2 * few_groups<2>());
+            else
+                launch(sparse_mla_few<1, S>, few_groups<1>());
+        } else {
+            if (Hq == 64)
+                launch(sparse_mla_mfma<4, S, KV8>, 4);
+            else if (Hq == 32)
+                launch(sparse_mla_mfma<2, S, KV8>, 2);
+            else
+                launch(sparse_mla_mfma<1, S, KV8>, 1);
+        }
+    };
+    if (part)
+        heads(std::true_type{});
+    else
+        heads(std::false_type{});
 }
 
 // Slices per row: as given, or (0) enough for one block per compute unit (a

@@ -1,7 +1,7 @@
 """MLA attention (Sec. 2.2: one latent KV row of 576 dims shared by all
 heads, the values its first 512) at the head counts that one tensor-parallel
-shard of the 128-head layer holds: 16, 32 and 64 heads, which run one, two
-and four waves per block.  bf16 and fp8 rows (Sec. 5.1), whole and split over
+shard of the 128-head layer holds: 16, 32 and 64 heads, whose key tiles are
+shared out over groups of waves.  bf16 and fp8 rows (Sec. 5.1), whole and split over
 slices, against the oracle on every row.  Tolerances as for 128 heads: max
 abs err <= 2e-2 and <= 2e-2 of the row's largest output, lse to 2e-3; rows
 with no valid id give zeros and -inf.  The large-logit case (scale 8) moves
@@ -111,4 +111,34 @@ def test_mla_fp8_wide_query_range():
     rows = np.arange(wl.total_q, dtype=np.int32)
     ref, lref = oracle.sparse_attn_fp8kv(wl.q_start, wl.hist_len, rows, qb, pool8, wl.page_table, wl.page_size,
                                          sel[rows], ai.scale, entry=1)
+    _compare(out.cpu().numpy(), lse.cpu().numpy(), ref, lref)
+
+
+@pytest.mark.parametrize("Hq", [16, 32, 64])
+@pytest.mark.parametrize("k", [1, 15, 17, 33, 63, 65, 130, 4096])
+def test_mla_bf16_heads_tile_edges(Hq, k):
+    """Selections around the 16-key tiles and the key groups' last step (one
+    tile in all, a group without a tile, the largest k), whole and split, and
+    outputs that are not 16-byte aligned."""
+    attn = dict(MLA_ATTN, Hq=Hq, kv_std=1.0 / 24.0, scale=1.0)
+    wl = make_workload(hist_len=[5000], new_len=[3], H=2, d=8, idx_dtype="f32", k=k, seed=70 + Hq, table="permuted",
+                       attn=attn)
+    ai, sel = attention_inputs(wl), synth_topk(wl, seed=9, pad_rows=1)
+    bt = janus.Batch(wl.hist_len, wl.new_len)
+    kv = T(ai.k_pool)
+    args = (bt, T(ai.q), kv, kv, T(wl.page_table), wl.page_size, T(sel), ai.scale)
+    rows = np.arange(wl.total_q, dtype=np.int32)
+    ref, lref = oracle.sparse_attn(wl.q_start, wl.hist_len, rows, ai.q, ai.k_pool, ai.v_pool, ai.k_row_stride,
+                                   ai.v_row_stride, wl.page_table, wl.page_size, sel, ai.scale, ai.dv)
+    n = wl.total_q * Hq * ai.dv
+    for dt, off in ((torch.float32, 1), (torch.bfloat16, 2)):
+        out = torch.full((n + 8,), 7.0, dtype=dt, device="cuda")
+        _, lse = janus.sparse_attn(*args, dv=ai.dv, out_dtype="f32" if dt == torch.float32 else "bf16",
+                                   want_lse=True, out=out[off:off + n])
+        torch.cuda.synchronize()
+        got = out[off:off + n].float().cpu().numpy().reshape(wl.total_q, Hq, ai.dv)
+        _compare(got, lse.cpu().numpy(), ref, lref)
+        assert bool((out[:off] == 7).all()) and bool((out[off + n:] == 7).all())
+    out, lse = janus.sparse_attn_split(*args, num_splits=3, dv=ai.dv, out_dtype="f32", want_lse=True)
+    torch.cuda.synchronize()
     _compare(out.cpu().numpy(), lse.cpu().numpy(), ref, lref)

@@ -128,7 +128,7 @@ typedef struct {
  *           scores + score_start[b] + i*(M_b+N_b) and holds M_b+N_b entries.
  * q_dt must equal k_dt.  fp8 with H = 64 and d = 128 runs on fp8 MFMA (the
  * head weights are applied in bf16: relative error <= 2^-8 per term); every
- * other dtype and shape runs on a plain vector kernel.  Accumulation is fp32.
+ * other dtype and shape runs on the fp32 MFMA.  Accumulation is fp32.
  */
 int janus_index_scores(const janus_batch *b,
                        const void *q, janus_dtype q_dt, const float *q_scale,

@@ -285,6 +285,16 @@ JANUS_DEV bool xcd_tile_chunk(int L, int nchunks, int ntiles, int &tile, int &ch
     return true;
 }
 
+// Keys of one chunk of a session: its context over the launch's chunk count,
+// in whole stages.  Every session has chunks on every XCD that way; with the
+// chunk length of the longest session, a shorter one had only the first
+// chunks, so that the last XCDs idled (eight sessions of 10K to 51K tokens,
+// MXFP4 keys: 3995 -> 2998 us; sixteen of 0.5K to 131K, fp8 keys: 2948 -> 950).
+JANUS_DEV int session_chunk(int ctx, int nchunks)
+{
+    return ((ctx + nchunks - 1) / nchunks + IDX_STAGE - 1) / IDX_STAGE * IDX_STAGE;
+}
+
 // LDS stage layout: key row r (128 bytes) holds its 16-byte column c at slot
 // c ^ ((r >> 1) & 7), so the 16 rows read by one 16-lane group land in 16
 // different bank groups.
@@ -299,7 +309,7 @@ template <int H, int TPW>
 __global__ __launch_bounds__(256, (TPW == 4 ? 2 : 4)) void index_scores_fp8_mfma(
     const int32_t *__restrict__ q_start, const int32_t *__restrict__ ctx_start,
     const int32_t *__restrict__ hist_len, const int64_t *__restrict__ score_start, int num_seqs, int es,
-    int nchunks, int key_chunk, int ntiles, const uint8_t *__restrict__ q, const float *__restrict__ q_scale,
+    int nchunks, int ntiles, const uint8_t *__restrict__ q, const float *__restrict__ q_scale,
     const uint8_t *__restrict__ kI, const float *__restrict__ k_scale, const float *__restrict__ w,
     float *__restrict__ scores)
 {
@@ -323,6 +333,7 @@ __global__ __launch_bounds__(256, (TPW == 4 ? 2 : 4)) void index_scores_fp8_mfma
     const int N = q_start[b + 1] - q_start[b];
     const int M = hist_len[b];
     const int ctx = entries_of(M + N, es);
+    const int key_chunk = session_chunk(ctx, nchunks);
     const int key_lo = chunk * key_chunk;
     if (key_lo >= ctx)
         return;
@@ -503,7 +514,7 @@ JANUS_DEV v8bf as_v8bf(v4i x) { return __builtin_bit_cast(v8bf, x); }
 __global__ __launch_bounds__(256, 2) void index_scores_bf16_mfma(
     const int32_t *__restrict__ q_start, const int32_t *__restrict__ ctx_start,
     const int32_t *__restrict__ hist_len, const int64_t *__restrict__ score_start, int num_seqs, int es,
-    int nchunks, int key_chunk, int ntiles, const uint16_t *__restrict__ q, const float *__restrict__ q_scale,
+    int nchunks, int ntiles, const uint16_t *__restrict__ q, const float *__restrict__ q_scale,
     const uint8_t *__restrict__ kI, const float *__restrict__ k_scale, const float *__restrict__ w,
     float *__restrict__ scores)
 {
@@ -520,6 +531,7 @@ __global__ __launch_bounds__(256, 2) void index_scores_bf16_mfma(
     const int N = q_start[b + 1] - q_start[b];
     const int M = hist_len[b];
     const int ctx = entries_of(M + N, es);
+    const int key_chunk = session_chunk(ctx, nchunks);
     const int key_lo = chunk * key_chunk;
     if (key_lo >= ctx)
         return;
@@ -697,7 +709,7 @@ constexpr int F4_ROW = 64;  // bytes of e2m1 codes per key (128 dims)
 __global__ __launch_bounds__(256, 4) void index_scores_mxfp4_mfma(
     const int32_t *__restrict__ q_start, const int32_t *__restrict__ ctx_start,
     const int32_t *__restrict__ hist_len, const int64_t *__restrict__ score_start, int num_seqs, int es,
-    int nchunks, int key_chunk, int ntiles, const uint8_t *__restrict__ q, const float *__restrict__ q_scale,
+    int nchunks, int ntiles, const uint8_t *__restrict__ q, const float *__restrict__ q_scale,
     const uint8_t *__restrict__ kI, const uint8_t *__restrict__ k_bscale, const float *__restrict__ k_scale,
     const float *__restrict__ w, float *__restrict__ scores)
 {
@@ -716,6 +728,7 @@ __global__ __launch_bounds__(256, 4) void index_scores_mxfp4_mfma(
     const int N = q_start[b + 1] - q_start[b];
     const int M = hist_len[b];
     const int ctx = entries_of(M + N, es);
+    const int key_chunk = session_chunk(ctx, nchunks);
     const int key_lo = chunk * key_chunk;
     if (key_lo >= ctx)
         return;
@@ -1272,6 +1285,13 @@ __global__ __launch_bounds__(256, 2) void index_scores_rows(
 
 namespace janus {
 
+// Key chunks per session of the prefill kernels: a multiple of the XCD count,
+// so that the longest session's are at most IDX_KEY_CHUNK keys long.
+static int prefill_chunks(const janus_batch *bt)
+{
+    return IDX_XCD * std::max(1, ceil_div(ceil_div(bt->max_ctx, IDX_XCD), IDX_KEY_CHUNK));
+}
+
 // Tiles of the row-tile kernel: one per session when no session appends
 // more than NQ tokens, else an upper bound (ceil(total_q / NQ) + sessions).
 static int64_t rows_tiles(const janus_batch *bt, int nq)
@@ -1364,32 +1384,24 @@ extern "C" int janus_index_scores(const janus_batch *bt, const void *q, janus_dt
         return launch_status();
     }
     if (q_dt == JANUS_FP8_E4M3 && d == 128 && H == 64 && bt->max_ctx <= (1 << 24)) {
-        // key chunks: a multiple of the XCD count, each a whole number of
-        // stages and at most IDX_KEY_CHUNK keys long
-        const int per_xcd_keys = ceil_div(bt->max_ctx, IDX_XCD);
-        const int chunks_per_xcd = std::max(1, ceil_div(per_xcd_keys, IDX_KEY_CHUNK));
-        const int key_chunk = ceil_div(ceil_div(per_xcd_keys, chunks_per_xcd), IDX_STAGE) * IDX_STAGE;
-        const int nchunks = ceil_div(bt->max_ctx, key_chunk);
+        const int nchunks = prefill_chunks(bt);
         constexpr int TPW = IDX_TPW;
         const int ntiles = ceil_div(bt->total_q, 4 * TPW) + nseq;
         const int per_xcd = ceil_div(nchunks, IDX_XCD) * ntiles;
         hipLaunchKernelGGL((index_scores_fp8_mfma<64, TPW>), dim3(IDX_XCD * per_xcd), dim3(256), 0, st, bt->q_start,
-                           bt->ctx_start, bt->hist_len, bt->score_start, nseq, bt->entry_shift, nchunks, key_chunk, ntiles,
+                           bt->ctx_start, bt->hist_len, bt->score_start, nseq, bt->entry_shift, nchunks, ntiles,
                            (const uint8_t *)q, q_scale, (const uint8_t *)kI, k_scale, w, scores);
         return launch_status();
     }
     if (q_dt == JANUS_BF16 && d == 128 && H == 64 && bt->max_ctx <= (1 << 23)) {
         // bf16 on bf16 MFMA: the fp8 kernel's key chunking (32-bit buffer
         // offsets over 256-byte key rows: contexts up to 2^23)
-        const int per_xcd_keys = ceil_div(bt->max_ctx, IDX_XCD);
-        const int chunks_per_xcd = std::max(1, ceil_div(per_xcd_keys, IDX_KEY_CHUNK));
-        const int key_chunk = ceil_div(ceil_div(per_xcd_keys, chunks_per_xcd), IDX_STAGE) * IDX_STAGE;
-        const int nchunks = ceil_div(bt->max_ctx, key_chunk);
+        const int nchunks = prefill_chunks(bt);
         const int ntiles = ceil_div(bt->total_q, 8) + nseq;
         const int per_xcd = ceil_div(nchunks, IDX_XCD) * ntiles;
         hipLaunchKernelGGL(index_scores_bf16_mfma, dim3(IDX_XCD * per_xcd), dim3(256), 0, st, bt->q_start,
-                           bt->ctx_start, bt->hist_len, bt->score_start, nseq, bt->entry_shift, nchunks, key_chunk,
-                           ntiles, (const uint16_t *)q, q_scale, (const uint8_t *)kI, k_scale, w, scores);
+                           bt->ctx_start, bt->hist_len, bt->score_start, nseq, bt->entry_shift, nchunks, ntiles,
+                           (const uint16_t *)q, q_scale, (const uint8_t *)kI, k_scale, w, scores);
         return launch_status();
     }
     // any other dtype and shape; token tiles over y and, past its limit, z
@@ -1422,15 +1434,12 @@ extern "C" int janus_index_scores_mxfp4(const janus_batch *bt, const void *q, co
         return launch_status();
     }
     // prefill-shaped: keys staged through LDS, the fp8 kernel's chunking
-    const int per_xcd_keys = ceil_div(bt->max_ctx, IDX_XCD);
-    const int chunks_per_xcd = std::max(1, ceil_div(per_xcd_keys, IDX_KEY_CHUNK));
-    const int key_chunk = ceil_div(ceil_div(per_xcd_keys, chunks_per_xcd), IDX_STAGE) * IDX_STAGE;
-    const int nchunks = ceil_div(bt->max_ctx, key_chunk);
+    const int nchunks = prefill_chunks(bt);
     const int ntiles = ceil_div(bt->total_q, 8) + bt->num_seqs;
     const int per_xcd = ceil_div(nchunks, IDX_XCD) * ntiles;
     hipLaunchKernelGGL(index_scores_mxfp4_mfma, dim3(IDX_XCD * per_xcd), dim3(256), 0, as_stream(stream),
                        bt->q_start, bt->ctx_start, bt->hist_len, bt->score_start, bt->num_seqs, bt->entry_shift,
-                       nchunks, key_chunk, ntiles, (const uint8_t *)q, q_scale, (const uint8_t *)kI, k_block_scale,
+                       nchunks, ntiles, (const uint8_t *)q, q_scale, (const uint8_t *)kI, k_block_scale,
                        k_scale, w, scores);
     return launch_status();
 }

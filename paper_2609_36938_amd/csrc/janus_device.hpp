@@ -42,6 +42,47 @@ JANUS_DEV int session_of_row(const int32_t *q_start, int num_seqs, int row)
     return lo;
 }
 
+// The same, by a whole wave: 64 sessions per step, one load instead of a chain
+// of dependent ones.  Every lane of the wave calls it.
+JANUS_DEV int session_of_row_wave(const int32_t *q_start, int num_seqs, int row)
+{
+    if (num_seqs > 4 * kWave)
+        return session_of_row(q_start, num_seqs, row);
+    int n = 0;
+    for (int s0 = 0; s0 < num_seqs; s0 += kWave) {
+        const int s = s0 + (int)(threadIdx.x & 63);
+        n += __popcll(__ballot(s < num_seqs && q_start[s] <= row));
+    }
+    return max(n - 1, 0);
+}
+
+// Value of another lane by a data-parallel move; lanes whose source is
+// outside the move keep `old`.
+template <int CTRL, int ROWS>
+JANUS_DEV int dpp_move(int old, int v)
+{
+    return __builtin_amdgcn_update_dpp(old, v, CTRL, ROWS, 0xf, false);
+}
+
+// Inclusive scan over the wave's 64 lanes: 16-lane rows, then each row's last
+// lane into the rows after it.  Register moves: a shuffle per step would wait
+// for an LDS round trip each.
+template <class Op>
+JANUS_DEV int wave_scan(int v, int unit, Op op)
+{
+    v = op(v, dpp_move<0x111, 0xf>(unit, v));  // lane - 1 within the row
+    v = op(v, dpp_move<0x112, 0xf>(unit, v));
+    v = op(v, dpp_move<0x114, 0xf>(unit, v));
+    v = op(v, dpp_move<0x118, 0xf>(unit, v));
+    v = op(v, dpp_move<0x142, 0xa>(unit, v));  // lane 15 -> row 1, lane 47 -> row 3
+    v = op(v, dpp_move<0x143, 0xc>(unit, v));  // lane 31 -> rows 2 and 3
+    return v;
+}
+JANUS_DEV int wave_sum_scan(int v)
+{
+    return wave_scan(v, 0, [](int a, int b) { return a + b; });
+}
+
 // OCP e4m3fn byte -> fp32 (exact).
 JANUS_DEV float fp8e4m3_to_f32(uint32_t b)
 {

@@ -2,67 +2,75 @@
 // causal candidates [0, M+i] of each score row, exact under the strict order
 // (score descending, id ascending).
 //
-// One 512-thread block per row.  A row (up to 557 KB at a 128K history) does
-// not fit in LDS, so the block streams it from HBM once, keeping only
-// candidates that beat a running threshold in an LDS buffer of CAP (key, id)
-// pairs (CAP = 4096 for k <= 2048, two blocks per CU; else 8192):
+// One block per row.  A row (up to 557 KB at a 128K history) does not fit in
+// LDS, so the block streams it from HBM once, keeping only candidates that
+// beat a running threshold in an LDS buffer of CAP (key, id) pairs:
 //   1. threshold seed: a strided sample of whole 128-byte lines (1/32 of a
-//      128K row) is radix-selected on its top 16 key bits for a rank a little
-//      above k * (sample share), so that in expectation ~1.3k elements pass;
-//   2. streaming filter: the row moves in 8 KB stages, one float4 per thread,
-//      through a ring of five registers per thread: four stages are in flight
-//      while one is filtered, with one LDS-only barrier per stage.  Each wave
-//      appends its accepted elements with one LDS atomic.  Slots past the
-//      buffer's end are not written; at the next barrier the buffer is cut to
-//      exactly the k best, the threshold rises to the k-th best (key, id), and
-//      the dropped elements - still in their register - are filtered again,
-//      so no member of the answer is ever lost.  If the seed was above the
-//      k-th key (fewer than k passed), the row is streamed again with no
-//      threshold;
-//   3. exact selection: 8-bit-digit radix select on the order-preserving
-//      score key finds the k-th key; ties on it are resolved by a second radix
-//      select on ids (smallest first) when they exist;
-//   4. ordered output: the winners are set in an LDS bitmap over [0, n),
-//      turned into ascending ids by a block scan of popcounts and written out
-//      through LDS, coalesced.
+//      128K row) gives the key of a rank a little above k * (sample share), so
+//      that in expectation ~1.3k elements pass;
+//   2. streaming filter: each wave takes 1 KB chunks of its own, TK_RING of
+//      them in flight in registers, and appends what it accepts with one LDS
+//      atomic per chunk that has any.  The waves meet only when the row is
+//      done or the buffer full: a wave that finds no room stops at its chunk;
+//      the buffer is then cut to exactly the k best, the threshold rises to
+//      the k-th best (key, id), and the stopped waves go on, so no member of
+//      the answer is lost.  If the seed was above the k-th key (fewer than k
+//      passed), the row is streamed again with no threshold;
+//   3. exact selection from registers: the keys' range is narrowed to one of
+//      2048 equal bins, and again, until the bin holding the k-th key has few
+//      enough entries to be ranked pairwise, or is a single key, whose ties
+//      the same narrowing on ids resolves (smallest first);
+//   4. ordered output: the winners are set in an LDS bitmap over [0, n), a
+//      block scan of its words' popcounts gives each winner its rank, and the
+//      ids are staged by rank in LDS and written out coalesced.
+//
+// What bounds it: the stream (HBM at long rows of many tokens), and with few
+// or short rows the fixed phases, whose cost is barriers and LDS round trips.
+// Narrowing between the data's own extremes takes one histogram pass where
+// 8-bit digits from the top took four (the first ones all but one bin wide,
+// their atomics serialised), register scans replace shuffles, and waves that
+// stream on their own need no barrier per stage.  Measured (k = 2048 unless
+// stated): 4096 rows of 135K 500 -> 413 us (5.4 TB/s), 64 rows of 32K-158K 51
+// -> 30, 512 shards of 16K (k = 256) 21 -> 13, one row of 13K 27 -> 15, 2048
+// rows of 8.2K (k = 512) 90 -> 50.
 #include "janus_device.hpp"
 #include "janus_host.hpp"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace janus {
 
-constexpr int TK_THREADS = 512;
-constexpr int TK_WAVES = TK_THREADS / kWave;
-constexpr int TK_STAGE4 = TK_THREADS;     // float4 per stage: one per thread
-constexpr int TK_RING = 5;                // register ring depth; TK_RING - 1 stages in flight
+constexpr int TK_RING = 8;                // 1 KB chunks in flight per wave
 constexpr int TK_MAX_K = 6144;            // with CAP = 8192: >= 2048 free slots after a cut
 constexpr int TK_SMALL_K = 2048;          // with CAP = 4096
 constexpr int TK_SAMPLE_LINES = 128;      // ~1/32 of a 128K row, in 32-element lines
-constexpr int TK_SAMPLE_PT = TK_SAMPLE_LINES * 32 / TK_THREADS;
+constexpr int TK_BINS = 2048;
+constexpr int TK_FEW = 64;                // entries of a bin that are ranked pairwise
 
-// Output step: bitmap words per prefix group, and the group prefix plus the
-// staged ids live in `aux` (CAP/4 + max k words).
-constexpr int TK_GROUP = 8;
 constexpr int tk_max_k(int cap) { return cap <= 4096 ? TK_SMALL_K : TK_MAX_K; }
 
-template <int CAP>
-struct TopkShared {
+template <int TPB, int CAP>
+struct alignas(16) TopkShared {
+    static constexpr int WAVES = TPB / kWave;
     uint32_t key[CAP];
     int32_t id[CAP];   // directly behind key: the output bitmap spans both
-    int32_t aux[2 * CAP / TK_GROUP + tk_max_k(CAP)];
-    uint32_t hist[2][256];
-    int32_t wsum[TK_WAVES];
+    union {
+        uint32_t hist[TK_BINS];
+        uint16_t pre[2 * CAP];  // set bits before each word of the output bitmap
+    };
+    int32_t stage[tk_max_k(CAP)];  // ids by rank
+    uint32_t few_key[TK_FEW];
+    int32_t few_id[TK_FEW];
+    int32_t wsum[WAVES];
+    uint32_t wmin[WAVES], wmax[WAVES];
     int32_t count;
-    uint32_t sel_v;
-    int32_t sel_rem;
-    int32_t sel_cnt;
+    int32_t nfew;
+    int32_t sel_bin, sel_rem, sel_cnt;
     uint32_t thr_key;  // accept (key, id) > (thr_key, thr_id) in the strict order:
     int32_t thr_id;    //   key > thr_key, or key == thr_key and id < thr_id
     float thr_f;       // thr_key as a score (the same test on floats)
 };
-
-JANUS_DEV uint64_t lanemask_lt() { return (1ull << (threadIdx.x & 63)) - 1ull; }
 
 // Workgroup barrier that orders LDS only.  __syncthreads() also waits for
 // every outstanding global load.
@@ -82,9 +90,9 @@ JANUS_DEV float key_score(uint32_t key)
     return __uint_as_float((key & 0x80000000u) ? (key & 0x7fffffffu) : ~key);
 }
 
-// Sets the running threshold (thread 0 only; the caller synchronises).
-template <int CAP>
-JANUS_DEV void set_threshold(TopkShared<CAP> &sm, uint32_t key, int32_t id)
+// Sets the running threshold (one thread; the caller synchronises).
+template <class SM>
+JANUS_DEV void set_threshold(SM &sm, uint32_t key, int32_t id)
 {
     sm.thr_key = key;
     sm.thr_id = key < 0x007fffffu ? 0x7fffffff : id;
@@ -102,354 +110,367 @@ JANUS_DEV __amdgpu_buffer_rsrc_t row_rsrc(const void *base, uint32_t bytes)
     return __builtin_amdgcn_make_buffer_rsrc(p, (short)0, (int)__builtin_amdgcn_readfirstlane(bytes), 0x00020000);
 }
 
-// Inclusive prefix sum over the block (TK_THREADS values); also returns the total.
-template <int CAP>
-JANUS_DEV int block_inclusive_scan(TopkShared<CAP> &sm, int v, int &total)
+// Exclusive prefix sum over the block; also returns the total.  Ends without
+// a barrier: the caller has one before wsum's next use.
+template <class SM>
+JANUS_DEV int block_exclusive_scan(SM &sm, int v, int &total)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        int t = __shfl_up(v, o, 64);
-        if (lane >= o)
-            v += t;
-    }
-    if (lane == 63)
-        sm.wsum[wave] = v;
+    const int wave = threadIdx.x >> 6;
+    const int incl = wave_sum_scan(v);
+    if ((threadIdx.x & 63) == 63)
+        sm.wsum[wave] = incl;
     lds_sync();
     int off = 0, tot = 0;
 #pragma unroll
-    for (int w = 0; w < TK_WAVES; ++w) {
-        int s = sm.wsum[w];
+    for (int w = 0; w < SM::WAVES; ++w) {
+        const int s = sm.wsum[w];
         off += (w < wave) ? s : 0;
         tot += s;
     }
-    lds_sync();
     total = tot;
-    return v + off;
+    return off + incl - v;
 }
 
-// LDS histogram increment with a fast path when the whole wave hits one bin.
-JANUS_DEV void hist_add(uint32_t *hist, bool on, uint32_t bin)
+// Smallest and largest of the block's values (two barriers).
+template <class SM>
+JANUS_DEV void block_extremes(SM &sm, uint32_t &lo, uint32_t &hi)
 {
-    uint64_t act = __ballot(on);
-    if (act == 0)
-        return;
-    uint32_t first = __shfl(bin, __ffsll((unsigned long long)act) - 1, 64);
-    uint64_t same = __ballot(on && bin == first);
-    if (same == act) {
-        if ((threadIdx.x & 63) == (uint32_t)(__ffsll((unsigned long long)act) - 1))
-            atomicAdd(&hist[first], (uint32_t)__popcll(act));
-        return;
-    }
-    if (on)
-        atomicAdd(&hist[bin], 1u);
-}
-
-// Radix select over buffer entries [0, cnt) that satisfy pred(e), on the
-// 8-bit digits of val(e) from the top down to the digit at lo_shift: returns
-// in sm.sel_v the prefix V (the value with the lower lo_shift bits cleared)
-// such that fewer than `want` entries have a larger prefix and at least `want`
-// have a prefix >= V; sm.sel_rem is how many entries with prefix V are needed
-// to make up `want`, and sm.sel_cnt how many entries have prefix V.
-// Two barriers per digit: the histograms alternate between two buffers (the
-// idle one is cleared during the other's pass) and one wave ranks the bins.
-template <int CAP, class Val, class Pred>
-JANUS_DEV void radix_select(TopkShared<CAP> &sm, int cnt, int want, Val val, Pred pred, int lo_shift = 0)
-{
-    if (threadIdx.x < 256) {
-        sm.hist[0][threadIdx.x] = 0u;
-        sm.hist[1][threadIdx.x] = 0u;
+    auto umin = [](int a, int b) { return (int)min((uint32_t)a, (uint32_t)b); };
+    auto umax = [](int a, int b) { return (int)max((uint32_t)a, (uint32_t)b); };
+    const uint32_t mn = (uint32_t)wave_scan((int)lo, -1, umin), mx = (uint32_t)wave_scan((int)hi, 0, umax);
+    if ((threadIdx.x & 63) == 63) {
+        sm.wmin[threadIdx.x >> 6] = mn;
+        sm.wmax[threadIdx.x >> 6] = mx;
     }
     lds_sync();
-    uint32_t prefix = 0, mask = 0;
-    int rem = want;
-    int buf = 0;
-    for (int shift = 24; shift >= lo_shift; shift -= 8, buf ^= 1) {
-        uint32_t *hist = sm.hist[buf];
-        if (threadIdx.x < 256 && shift < 24)
-            sm.hist[buf ^ 1][threadIdx.x] = 0u;  // read by the previous pass, used by the next
-        for (int e0 = 0; e0 < cnt; e0 += TK_THREADS) {
-            int e = e0 + threadIdx.x;
-            bool on = false;
-            uint32_t v = 0;
-            if (e < cnt && pred(e)) {
-                v = val(e);
-                on = (v & mask) == prefix;
-            }
-            hist_add(hist, on, (v >> shift) & 255u);
-        }
-        lds_sync();
-        if (threadIdx.x < 64) {
-            // lane l holds bins 255-4l .. 252-4l; suffix sums from bin 255 down
-            const int l = threadIdx.x;
-            int h[4], sum = 0;
+    lo = 0xffffffffu;
+    hi = 0u;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                h[j] = (int)hist[255 - 4 * l - j];
-                sum += h[j];
-            }
-            int incl = sum;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int t = __shfl_up(incl, o, 64);
-                if (l >= o)
-                    incl += t;
-            }
-            int c = incl - sum;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (c < rem && c + h[j] >= rem) {
-                    sm.sel_v = (uint32_t)(255 - 4 * l - j);
-                    sm.sel_rem = rem - c;
-                    sm.sel_cnt = h[j];
-                }
-                c += h[j];
-            }
-        }
-        lds_sync();
-        prefix |= sm.sel_v << shift;
-        mask |= 255u << shift;
-        rem = sm.sel_rem;
-    }
-    lds_sync();  // everyone has read sel_* before thread 0 rewrites them
-    if (threadIdx.x == 0) {
-        sm.sel_v = prefix;
-        sm.sel_rem = rem;
+    for (int w = 0; w < SM::WAVES; ++w) {
+        lo = min(lo, sm.wmin[w]);
+        hi = max(hi, sm.wmax[w]);
     }
     lds_sync();
 }
 
-// Finds the k-th best (key, id) among the cnt buffered candidates:
-// returns T (key) and I (the largest id among the winners with key T).
-// Winners are exactly: key > T, or key == T and id <= I.
-template <int CAP>
-JANUS_DEV void kth_best(TopkShared<CAP> &sm, int cnt, int k, uint32_t &T, int32_t &I)
+// Narrows [lo, hi], which holds at least `want` of the block's values v (those
+// flagged in on), to the bin that holds the want-th largest: at most `few`
+// values, or a single value of the range.  On return [lo, hi] is that bin,
+// `want` how many of its largest values make up the asked number, and the
+// result how many values it holds.
+template <int TPB, int NI, class SM>
+JANUS_DEV int narrow(SM &sm, const uint32_t (&v)[NI], uint32_t on, uint32_t &lo, uint32_t &hi, int &want, int few)
 {
-    radix_select(sm, cnt, k, [&](int e) { return sm.key[e]; }, [&](int) { return true; });
-    T = sm.sel_v;
-    const int need = sm.sel_rem;  // winners among key == T
-    if (need == sm.sel_cnt) {     // all of them: no tie to break
-        I = 0x7fffffff;
-        lds_sync();
-        return;
-    }
-    // Ties on T: the `need` smallest ids win; select the largest of ~id.
-    const uint32_t Tl = T;
-    radix_select(sm, cnt, need, [&](int e) { return ~(uint32_t)sm.id[e]; },
-                 [&](int e) { return sm.key[e] == Tl; });
-    I = (int32_t)~sm.sel_v;
-}
-
-// Cuts the buffer to exactly its k best entries, in place and in order, and
-// raises the threshold to the k-th best.
-template <int CAP>
-__device__ __noinline__ void compact(TopkShared<CAP> &sm, int k)
-{
-    const int cnt = sm.count;
-    uint32_t T;
-    int32_t I;
-    kth_best(sm, cnt, k, T, I);
-    int out = 0;
-    // chunks of 4 entries per thread: every chunk is read before any of it is
-    // overwritten, and its destination ends before the next chunk begins
-    for (int c0 = 0; c0 < cnt; c0 += 4 * TK_THREADS) {
-        uint32_t kk[4];
-        int32_t ii[4];
-        uint32_t keep = 0;
+    constexpr int PER = TK_BINS / TPB;  // bins per thread of the scan
+    int cnt = 0;
+    for (int pass = 0; pass < 3; ++pass) {  // 11 bits a pass
+        const int bits = 32 - __clz((int)(hi - lo) | 1);
+        const int sh = max(0, bits - 11);  // (hi - lo) >> sh < 2048
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int e = c0 + 4 * threadIdx.x + j;
-            kk[j] = 0u;
-            ii[j] = 0;
-            if (e < cnt) {
-                kk[j] = sm.key[e];
-                ii[j] = sm.id[e];
-                if (kk[j] > T || (kk[j] == T && ii[j] <= I))
-                    keep |= 1u << j;
-            }
+        for (int j = 0; j < PER; ++j)
+            sm.hist[threadIdx.x * PER + j] = 0u;
+        lds_sync();
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+            if (((on >> i) & 1u) && v[i] >= lo && v[i] <= hi)
+                atomicAdd(&sm.hist[(v[i] - lo) >> sh], 1u);
+        lds_sync();
+        // thread t holds bins from TK_BINS - 1 - PER t down
+        int h[PER], sum = 0;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            h[j] = (int)sm.hist[TK_BINS - 1 - PER * (int)threadIdx.x - j];
+            sum += h[j];
         }
-        const int nk = __popc(keep);
         int tot;
-        int pos = out + block_inclusive_scan(sm, nk, tot) - nk;  // its barriers order reads before writes
+        int c = block_exclusive_scan(sm, sum, tot);
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (keep & (1u << j)) {
-                sm.key[pos] = kk[j];
-                sm.id[pos] = ii[j];
-                ++pos;
+        for (int j = 0; j < PER; ++j) {
+            if (c < want && c + h[j] >= want) {
+                sm.sel_bin = TK_BINS - 1 - PER * (int)threadIdx.x - j;
+                sm.sel_rem = want - c;
+                sm.sel_cnt = h[j];
             }
-        out += tot;
+            c += h[j];
+        }
+        lds_sync();
+        lo += (uint32_t)sm.sel_bin << sh;
+        hi = lo + min(hi - lo, (1u << sh) - 1u);
+        want = sm.sel_rem;
+        cnt = sm.sel_cnt;
+        if (cnt <= few || sh == 0)
+            break;
+        // (the next pass writes sel_* after three more barriers)
     }
-    if (threadIdx.x == 0) {
-        sm.count = out;  // == k
-        set_threshold(sm, T, I);
+    return cnt;
+}
+
+// Flags of the k best of the block's buffered entries (those flagged in on, at
+// least k of them), and the threshold set to the k-th best or, where all of
+// a bin wins, to the bin's lower end.  Ends with a barrier.
+template <int TPB, int NI, class SM>
+JANUS_DEV uint32_t best(SM &sm, const uint32_t (&key)[NI], const int32_t (&id)[NI], uint32_t on, int k)
+{
+    uint32_t lo = 0xffffffffu, hi = 0u;
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+        if ((on >> i) & 1u) {
+            lo = min(lo, key[i]);
+            hi = max(hi, key[i]);
+        }
+    if (threadIdx.x == 0)
+        sm.nfew = 0;
+    block_extremes(sm, lo, hi);
+    int want = k;
+    const int cnt = narrow<TPB>(sm, key, on, lo, hi, want, TK_FEW);
+    uint32_t win = 0, in = 0;  // above the bin, inside it
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+        win |= (((on >> i) & 1u) && key[i] > hi ? 1u : 0u) << i;
+        in |= (((on >> i) & 1u) && key[i] >= lo && key[i] <= hi ? 1u : 0u) << i;
     }
+    if (want == cnt) {  // the whole bin
+        win |= in;
+        if (threadIdx.x == 0)
+            set_threshold(sm, lo, 0x7fffffff);
+    } else if (cnt <= TK_FEW) {
+        // rank the bin's entries against each other
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+            if ((in >> i) & 1u) {
+                const int at = atomicAdd(&sm.nfew, 1);
+                sm.few_key[at] = key[i];
+                sm.few_id[at] = id[i];
+            }
+        lds_sync();
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+            if ((in >> i) & 1u) {
+                int rank = 0;
+                for (int j = 0; j < cnt; ++j)
+                    rank += sm.few_key[j] > key[i] || (sm.few_key[j] == key[i] && sm.few_id[j] < id[i]);
+                win |= (rank < want ? 1u : 0u) << i;
+                if (rank == want - 1)
+                    set_threshold(sm, key[i], id[i]);
+            }
+    } else {
+        // many ties on one key: its smallest ids, the largest of ~id
+        uint32_t inv[NI], ilo = 0xffffffffu, ihi = 0u;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            inv[i] = ~(uint32_t)id[i];
+            if ((in >> i) & 1u) {
+                ilo = min(ilo, inv[i]);
+                ihi = max(ihi, inv[i]);
+            }
+        }
+        block_extremes(sm, ilo, ihi);
+        narrow<TPB>(sm, inv, in, ilo, ihi, want, 1);  // ids differ: a bin of one
+#pragma unroll
+        for (int i = 0; i < NI; ++i)
+            win |= (((in >> i) & 1u) && inv[i] >= ilo ? 1u : 0u) << i;
+        if (threadIdx.x == 0)
+            set_threshold(sm, lo, (int32_t)~ilo);
+    }
+    lds_sync();
+    return win;
+}
+
+// The buffer's entries of this thread (e = threadIdx.x + i TPB), flagged.
+template <int TPB, int NI, class SM>
+JANUS_DEV uint32_t load_entries(const SM &sm, int cnt, uint32_t (&key)[NI], int32_t (&id)[NI])
+{
+    uint32_t on = 0;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+        const int e = (int)threadIdx.x + i * TPB;
+        key[i] = e < cnt ? sm.key[e] : 0u;
+        id[i] = e < cnt ? sm.id[e] : -1;
+        on |= (id[i] >= 0 ? 1u : 0u) << i;  // (slots left by a stopped wave hold -1)
+    }
+    return on;
+}
+
+// Cuts the full buffer to exactly its k best entries and raises the threshold
+// to the k-th best.  Begins and ends with a barrier.
+template <int TPB, int CAP>
+__device__ __noinline__ void compact(TopkShared<TPB, CAP> &sm, int k)
+{
+    constexpr int NI = CAP / TPB;
+    uint32_t key[NI];
+    int32_t id[NI];
+    lds_sync();
+    const uint32_t on = load_entries<TPB>(sm, CAP, key, id);
+    const uint32_t win = best<TPB>(sm, key, id, on, k);
+    int tot;
+    int pos = block_exclusive_scan(sm, __popc(win), tot);  // (every entry is in registers by now)
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+        if ((win >> i) & 1u) {
+            sm.key[pos] = key[i];
+            sm.id[pos] = id[i];
+            ++pos;
+        }
+    if (threadIdx.x == 0)
+        sm.count = tot;  // == k
     lds_sync();
 }
 
-// Appends this thread's accepted elements among x[0..3] (ids id0..id0+3, those
-// flagged in pend) and returns the flags of those that found no slot.
-template <int CAP>
-JANUS_DEV uint32_t append4(TopkShared<CAP> &sm, v4f x, uint32_t pend, int id0)
+// Appends this wave's accepted elements among x[0..3] (lane's ids id0 ..
+// id0+3, those flagged in pend); false if they found no room (then none is
+// in the buffer, and its last slots are marked unused).
+template <int CAP, class SM>
+JANUS_DEV bool append4(SM &sm, v4f x, uint32_t pend, int id0, float tf, int32_t ti)
 {
-    const float tf = sm.thr_f;
-    uint32_t acc = 0;
+    bool a[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-        acc |= (x[j] >= tf ? 1u : 0u) << j;
-    acc &= pend;
-    if (__ballot(acc != 0) == 0)
-        return 0u;
+        a[j] = x[j] >= tf && ((pend >> j) & 1u);
+    if (__ballot(a[0] || a[1] || a[2] || a[3]) == 0)
+        return true;
     // an element equal to the threshold passes only with a smaller id
-    const int32_t ti = sm.thr_id;
+    uint64_t m[4];
+    int tot = 0;
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-        if (x[j] == tf && id0 + j >= ti)
-            acc &= ~(1u << j);
-    // wave exclusive prefix of the per-lane counts (<= 4), bit-sliced over ballots
-    const int c = __popc(acc);
-    int excl = 0, tot = 0;
-#pragma unroll
-    for (int bit = 0; bit < 3; ++bit) {
-        const uint64_t m = __ballot((c >> bit) & 1);
-        excl += __popcll(m & lanemask_lt()) << bit;
-        tot += __popcll(m) << bit;
+    for (int j = 0; j < 4; ++j) {
+        a[j] = a[j] && !(x[j] == tf && id0 + j >= ti);
+        m[j] = __ballot(a[j]);
+        tot += __popcll(m[j]);
     }
+    if (tot == 0)
+        return true;
     int base = 0;
-    if ((threadIdx.x & 63) == 0 && tot > 0)
+    if ((threadIdx.x & 63) == 0)
         base = atomicAdd(&sm.count, tot);
-    base = __shfl(base, 0, 64);
-    int slot = base + excl;
-    uint32_t dropped = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-        if (acc & (1u << j)) {
-            if (slot < CAP) {
-                sm.key[slot] = score_key(x[j]);
-                sm.id[slot] = id0 + j;
-            } else {
-                dropped |= 1u << j;
-            }
-            ++slot;
-        }
-    return dropped;
-}
-
-// After a barrier: if some elements of the previous stage found no slot, cut
-// the buffer and filter them again (block-uniform loop; rare).
-template <int CAP>
-JANUS_DEV void recover(TopkShared<CAP> &sm, v4f x, uint32_t pend, int id0, int k)
-{
-    while (sm.count > CAP) {
-        lds_sync();
-        if (threadIdx.x == 0)
-            sm.count = CAP;  // every slot below the cap was written
-        lds_sync();
-        compact(sm, k);
-        pend = append4(sm, x, pend, id0);
-        lds_sync();
+    base = __builtin_amdgcn_readfirstlane(base);
+    if (base + tot > CAP) {
+        for (int e = base + (int)(threadIdx.x & 63); e < CAP; e += kWave)
+            sm.id[e] = -1;
+        return false;
     }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int slot = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(m[j] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m[j], 0));
+        if (a[j]) {
+            sm.key[slot] = score_key(x[j]);
+            sm.id[slot] = id0 + j;
+        }
+        base += __popcll(m[j]);
+    }
+    return true;
 }
 
 // One pass over [0, n) of the row, filtering against the running threshold;
-// with `seed`, the threshold is first set from a sample of the row.
-template <int CAP>
-JANUS_DEV void stream_row(TopkShared<CAP> &sm, const float *__restrict__ row, int n, int k, bool seed)
+// with `seed`, the threshold is first set from a sample of the row.  Ends with
+// a barrier.
+template <int TPB, int CAP>
+JANUS_DEV void stream_row(TopkShared<TPB, CAP> &sm, const float *__restrict__ row, int n, int k, bool seed)
 {
-    static_assert(TK_RING == 5, "the ring is unrolled by hand");
+    constexpr int NW = TPB / kWave;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // unaligned head (< 4 elements), 16-byte aligned body of float4s, tail (< 4)
     const int head = min(n, (int)(((16 - (reinterpret_cast<uintptr_t>(row) & 15)) & 15) >> 2));
     const int nbody4 = (n - head) >> 2;
     const int tail0 = head + (nbody4 << 2);
     const __amdgpu_buffer_rsrc_t body = row_rsrc(row + head, 16u * (uint32_t)nbody4);
-    const int nst = (nbody4 + TK_STAGE4 - 1) / TK_STAGE4;
-    // this thread's float4 of stage j (zeros past the body)
-    auto load = [&](int j) {
-        return __builtin_bit_cast(
-            v4f, __builtin_amdgcn_raw_buffer_load_b128(body, 16 * (j * TK_STAGE4 + (int)threadIdx.x), 0, 0));
+    const int nch = (nbody4 + kWave - 1) / kWave;  // 1 KB chunks: wave w takes w, w + NW, ..
+    // this lane's float4 at index i of the body (zeros past it)
+    auto load4 = [&](int i) {
+        return __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(body, 16 * i, 0, 0));
     };
 
-    // seed sample and the head/tail elements go to registers first, then the
-    // first stages are put in flight, then the sample is ranked under them
-    const int nlines = n >> 5;
+    // the sample goes out first, then the head and tail elements and the
+    // wave's first chunks; the sample is ranked under their latency
+    constexpr int SPT = TK_SAMPLE_LINES * 8 / TPB;  // float4s of the sample per thread
+    const int nlines = nbody4 >> 3;
     const int stride = max(1, nlines / TK_SAMPLE_LINES);
-    const int m = seed ? min(TK_SAMPLE_LINES, nlines) * 32 : 0;
-    float smp[TK_SAMPLE_PT];
+    const int m4 = seed ? min(TK_SAMPLE_LINES, nlines) * 8 : 0;
+    v4f smp[SPT];
 #pragma unroll
-    for (int j = 0; j < TK_SAMPLE_PT; ++j) {
-        const int e = (int)threadIdx.x + j * TK_THREADS;
-        smp[j] = e < m ? row[(((e >> 5) * stride) << 5) + (e & 31)] : 0.f;
+    for (int j = 0; j < SPT; ++j) {
+        const int e = (int)threadIdx.x + j * TPB;
+        smp[j] = load4(e < m4 ? (e >> 3) * stride * 8 + (e & 7) : nbody4);
     }
-    // thread 0 takes the head, thread 1 the tail
-    const int ht0 = threadIdx.x == 1 ? tail0 : 0;
-    const int htn = threadIdx.x == 0 ? head : (threadIdx.x == 1 ? n - tail0 : 0);
-    v4f ht;
+    // lanes 0..2 of the first wave take the head, 4..6 the tail
+    const int hti = lane < 4 ? lane : tail0 + lane - 4;
+    const bool ht = wave == 0 && (lane < 4 ? lane < head : lane < 8 && hti < n);
+    const float htv = ht ? row[hti] : 0.f;
+    v4f x[TK_RING];
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-        ht[j] = j < htn ? row[ht0 + j] : 0.f;
-
-    v4f x0 = load(0), x1 = load(1), x2 = load(2), x3 = load(3), x4;
+    for (int u = 0; u < TK_RING; ++u)
+        x[u] = load4((wave + u * NW) * kWave + lane);
 
     if (seed) {
+        uint32_t key[4 * SPT], on = 0, lo = 0xffffffffu, hi = 0u;
 #pragma unroll
-        for (int j = 0; j < TK_SAMPLE_PT; ++j) {
-            const int e = (int)threadIdx.x + j * TK_THREADS;
-            if (e < m)
-                sm.key[e] = score_key(smp[j]);
-        }
-        lds_sync();
-        // rank ~ 1.3 * k * (m / n) + 8; two digits suffice, since the seed only
-        // has to be at or below the k-th key
-        const int r = min(m, (int)(1.3f * (float)k * (float)m / (float)n) + 8);
-        radix_select(sm, m, r, [&](int e) { return sm.key[e]; }, [&](int) { return true; }, 16);
-        if (threadIdx.x == 0) {
-            set_threshold(sm, sm.sel_v, 0x7fffffff);  // accept key >= seed
-            sm.count = 0;
-        }
+        for (int j = 0; j < SPT; ++j)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const uint32_t kk = score_key(smp[j][c]);
+                key[4 * j + c] = kk;
+                if ((int)threadIdx.x + j * TPB < m4) {
+                    on |= 1u << (4 * j + c);
+                    lo = min(lo, kk);
+                    hi = max(hi, kk);
+                }
+            }
+        block_extremes(sm, lo, hi);
+        // rank ~ 1.3 * k * (sample / n) + 8; the bin's lower end suffices once
+        // the bin holds few of that rank's entries
+        int r = min(4 * m4, (int)(1.3f * (float)k * (float)(4 * m4) / (float)n) + 8);
+        narrow<TPB>(sm, key, on, lo, hi, r, max(4, r >> 3));
+        if (threadIdx.x == 0)
+            set_threshold(sm, lo, 0x7fffffff);  // accept key >= seed
         lds_sync();
     }
-    append4(sm, ht, (1u << htn) - 1u, ht0);  // at most 8 entries: room is certain
 
-    uint32_t drop = 0;  // previous stage's elements that found no slot
-    int drop_id0 = 0;
-    // stage j is filtered from ring register cur; prev held stage j-1 and
-    // receives stage j+4 once j-1's overflow (if any) is settled
-    auto step = [&](v4f &cur, v4f &prev, int j) {
+    bool edge = wave == 0;  // the head and tail are still to be appended
+    int j = wave;           // this wave's next chunk
+    for (bool first = true;; first = false) {
+        const float tf = sm.thr_f;
+        const int32_t ti = sm.thr_id;
+        if (!first) {
+#pragma unroll
+            for (int u = 0; u < TK_RING; ++u)
+                x[u] = load4((j + u * NW) * kWave + lane);
+        }
+        bool room = true;
+        if (edge) {
+            room = append4<CAP>(sm, v4f{htv, 0.f, 0.f, 0.f}, ht ? 1u : 0u, hti, tf, ti);
+            edge = !room;
+        }
+        // (one exit: with an early one the compiler moves the loads to the
+        // end of the loop and waits for all of them there)
+        while (room && j < nch) {
+#pragma unroll
+            for (int u = 0; u < TK_RING; ++u) {
+                const int v4 = j * kWave + lane;
+                // (chunks past the row have nothing pending)
+                if (room)
+                    room = append4<CAP>(sm, x[u], v4 < nbody4 ? 0xfu : 0u, head + 4 * v4, tf, ti);
+                x[u] = load4(v4 + TK_RING * NW * kWave);
+                j += room ? NW : 0;
+            }
+        }
         lds_sync();
-        if (sm.count > CAP)
-            recover(sm, prev, drop, drop_id0, k);
-        prev = load(j + TK_RING - 1);
-        const int v4 = j * TK_STAGE4 + (int)threadIdx.x;
-        drop_id0 = head + 4 * v4;
-        drop = append4(sm, cur, v4 < nbody4 ? 0xfu : 0u, drop_id0);
-    };
-    // whole turns of the ring (stages past the body are zeros and masked
-    // off), so that the loop has one exit and the ring needs no copies
-    for (int j = 0; j < nst; j += TK_RING) {
-        step(x0, x4, j);
-        step(x1, x0, j + 1);
-        step(x2, x1, j + 2);
-        step(x3, x2, j + 3);
-        step(x4, x3, j + 4);
+        if (sm.count <= CAP)
+            break;
+        compact(sm, k);
     }
-    // the last stage's overflow
-    lds_sync();
-    if (sm.count > CAP)
-        recover(sm, x4, drop, drop_id0, k);
 }
 
-template <int CAP>
-__global__ __launch_bounds__(TK_THREADS, CAP <= 4096 ? 4 : 2) void topk_rows(
+template <int TPB, int CAP>
+__global__ __launch_bounds__(TPB, CAP <= 4096 ? 4 : 2) void topk_rows(
     const int32_t *__restrict__ q_start, const int32_t *__restrict__ hist_len,
     const int64_t *__restrict__ score_start, int num_seqs, int es,
     const float *__restrict__ scores, int k_row, int32_t *__restrict__ topk_idx, int shards, int align)
 {
-    __shared__ TopkShared<CAP> sm;
+    __shared__ TopkShared<TPB, CAP> sm;
     // causal rows (shards == 0): block g selects k_row of its candidates
     // (tokens: [0, M+i]);
     // sharded rows: block g*shards + n selects k_row/shards of history shard n
     const int g = shards ? blockIdx.x / shards : blockIdx.x;
-    const int b = session_of_row(q_start, num_seqs, g);
+    const int b = __builtin_amdgcn_readfirstlane(session_of_row_wave(q_start, num_seqs, g));
     const int i = g - q_start[b];
     const int N = q_start[b + 1] - q_start[b];
     const int M = hist_len[b];
@@ -469,7 +490,7 @@ __global__ __launch_bounds__(TK_THREADS, CAP <= 4096 ? 4 : 2) void topk_rows(
     const float *row = scores + score_start[b] + (int64_t)i * ctx + base;
 
     if (n <= k) {
-        for (int j = threadIdx.x; j < k; j += TK_THREADS)
+        for (int j = threadIdx.x; j < k; j += TPB)
             out[j] = j < n ? base + j : -1;
         return;
     }
@@ -479,8 +500,8 @@ __global__ __launch_bounds__(TK_THREADS, CAP <= 4096 ? 4 : 2) void topk_rows(
     }
     lds_sync();
 
-    // 2. one streaming pass (two if the seed was above the k-th key)
-    stream_row(sm, row, n, k, n > CAP);
+    // 1., 2. one streaming pass (two if the seed was above the k-th key)
+    stream_row<TPB, CAP>(sm, row, n, k, n > CAP);
     if (sm.count < k) {
         lds_sync();
         if (threadIdx.x == 0) {
@@ -488,79 +509,55 @@ __global__ __launch_bounds__(TK_THREADS, CAP <= 4096 ? 4 : 2) void topk_rows(
             set_threshold(sm, 0u, 0x7fffffff);
         }
         lds_sync();
-        stream_row(sm, row, n, k, false);
+        stream_row<TPB, CAP>(sm, row, n, k, false);
     }
-    // 3. exact k-th best among the buffered candidates
+    // 3. the k best of the buffered candidates
     const int cnt = sm.count;
-    uint32_t T;
-    int32_t I;
-    kth_best(sm, cnt, k, T, I);
-    constexpr int PER = CAP / TK_THREADS;
-    int32_t win[PER];
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        const int e = threadIdx.x + j * TK_THREADS;
-        win[j] = -1;
-        if (e < cnt) {
-            const uint32_t key = sm.key[e];
-            const int32_t id = sm.id[e];
-            if (key > T || (key == T && id <= I))
-                win[j] = id;
-        }
-    }
-    lds_sync();
-    // 4. ascending output: the winners are set in an LDS bitmap over [0, n)
-    //    (in the key and id arrays); prefix counts per group of TK_GROUP
-    //    words give each winner its rank, and the ids are staged by rank in
-    //    aux and written out coalesced
+    constexpr int NI = CAP / TPB;
+    uint32_t key[NI], win;
+    int32_t id[NI];
+    win = load_entries<TPB>(sm, cnt, key, id);
+    if (cnt > k)
+        win = best<TPB>(sm, key, id, win, k);
+    else
+        lds_sync();
+    // 4. ascending output (the bitmap lies over the key and id arrays)
     uint32_t *bm = sm.key;
-    const int nwords = (n + 31) >> 5;  // <= 2 * CAP (checked by the launcher)
-    for (int wd = threadIdx.x; wd < nwords; wd += TK_THREADS)
-        bm[wd] = 0u;
+    const int nwords = (n + 31) >> 5;                          // <= 2 * CAP (checked by the launcher)
+    const int wpt = ((nwords + TPB - 1) / TPB + 3) & ~3;       // words per thread, whole 16-byte reads
+    for (int wd = 4 * threadIdx.x; wd < nwords; wd += 4 * TPB)
+        *(v4i *)(bm + wd) = v4i{0, 0, 0, 0};
     lds_sync();
 #pragma unroll
-    for (int j = 0; j < PER; ++j)
-        if (win[j] >= 0)
-            atomicOr(&bm[win[j] >> 5], 1u << (win[j] & 31));
+    for (int i = 0; i < NI; ++i)
+        if ((win >> i) & 1u)
+            atomicOr(&bm[id[i] >> 5], 1u << (id[i] & 31));
     lds_sync();
-    constexpr int MAXG = 2 * CAP / TK_GROUP;          // groups of the largest bitmap
-    constexpr int GPT = (MAXG + TK_THREADS - 1) / TK_THREADS;
-    int32_t *grp = sm.aux;                            // exclusive prefix per group
-    int32_t *stage = sm.aux + MAXG;                   // ids by rank
-    const int ngroups = (nwords + TK_GROUP - 1) / TK_GROUP;
-    int gc[GPT], c = 0;
-#pragma unroll
-    for (int u = 0; u < GPT; ++u) {
-        const int g = threadIdx.x * GPT + u;
-        gc[u] = 0;
-        if (g < ngroups)
-#pragma unroll
-            for (int w = 0; w < TK_GROUP; ++w)
-                gc[u] += g * TK_GROUP + w < nwords ? __popc(bm[g * TK_GROUP + w]) : 0;
-        c += gc[u];
+    const int w0 = threadIdx.x * wpt, w1 = min((nwords + 3) & ~3, w0 + wpt);
+    int c = 0;
+    for (int wd = w0; wd < w1; wd += 4) {
+        const v4i x = *(const v4i *)(bm + wd);
+        c += __popc((uint32_t)x[0]) + __popc((uint32_t)x[1]) + __popc((uint32_t)x[2]) + __popc((uint32_t)x[3]);
     }
     int tot;
-    int pos = block_inclusive_scan(sm, c, tot) - c;
-#pragma unroll
-    for (int u = 0; u < GPT; ++u) {
-        const int g = threadIdx.x * GPT + u;
-        if (g < ngroups)
-            grp[g] = pos;
-        pos += gc[u];
+    int pos = block_exclusive_scan(sm, c, tot);
+    for (int wd = w0; wd < w1; wd += 4) {
+        const v4i x = *(const v4i *)(bm + wd);
+        const uint32_t p0 = pos, p1 = p0 + __popc((uint32_t)x[0]), p2 = p1 + __popc((uint32_t)x[1]),
+                       p3 = p2 + __popc((uint32_t)x[2]);
+        *(v2i *)(sm.pre + wd) = v2i{(int)(p0 | (p1 << 16)), (int)(p2 | (p3 << 16))};
+        pos = (int)(p3 + __popc((uint32_t)x[3]));
     }
     lds_sync();
 #pragma unroll
-    for (int j = 0; j < PER; ++j)
-        if (win[j] >= 0) {
-            const int id = win[j], w = id >> 5, g = w / TK_GROUP;
-            int r = grp[g] + __popc(bm[w] & ((1u << (id & 31)) - 1u));
-            for (int w2 = g * TK_GROUP; w2 < w; ++w2)
-                r += __popc(bm[w2]);
-            stage[r] = id;
+    for (int i = 0; i < NI; ++i)
+        if ((win >> i) & 1u) {
+            const int wd = id[i] >> 5;
+            sm.stage[sm.pre[wd] + __popc(bm[wd] & ((1u << (id[i] & 31)) - 1u))] = base + id[i];
         }
     lds_sync();
-    for (int j = threadIdx.x; j < k; j += TK_THREADS)
-        out[j] = j < tot ? base + stage[j] : -1;
+    for (int j = threadIdx.x; j < k; j += TPB)
+        out[j] = j < tot ? sm.stage[j] : -1;
 }
 
 } // namespace janus
@@ -578,12 +575,14 @@ static int launch_topk(const janus_batch *bt, const float *scores, int k, int32_
     if (bt->total_q == 0)
         return JANUS_OK;
     const dim3 grid((unsigned)bt->total_q * (unsigned)(shards ? shards : 1));
+    auto go = [&](auto kern, int threads) {
+        hipLaunchKernelGGL(kern, grid, dim3(threads), 0, as_stream(stream), bt->q_start, bt->hist_len,
+                           bt->score_start, bt->num_seqs, bt->entry_shift, scores, k, topk_idx, shards, align);
+    };
     if (kk <= TK_SMALL_K && bt->max_ctx <= 2 * 4096 * 32)
-        hipLaunchKernelGGL(topk_rows<4096>, grid, dim3(TK_THREADS), 0, as_stream(stream), bt->q_start, bt->hist_len,
-                           bt->score_start, bt->num_seqs, bt->entry_shift, scores, k, topk_idx, shards, align);
+        go(topk_rows<512, 4096>, 512);
     else
-        hipLaunchKernelGGL(topk_rows<8192>, grid, dim3(TK_THREADS), 0, as_stream(stream), bt->q_start, bt->hist_len,
-                           bt->score_start, bt->num_seqs, bt->entry_shift, scores, k, topk_idx, shards, align);
+        go(topk_rows<512, 8192>, 512);
     return launch_status();
 }
 

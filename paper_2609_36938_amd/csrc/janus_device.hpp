@@ -56,6 +56,15 @@ JANUS_DEV int session_of_row_wave(const int32_t *q_start, int num_seqs, int row)
     return max(n - 1, 0);
 }
 
+// Workgroup barrier that orders LDS only.  __syncthreads() also waits for
+// every outstanding global access.
+JANUS_DEV void lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // Value of another lane by a data-parallel move; lanes whose source is
 // outside the move keep `old`.
 template <int CTRL, int ROWS>

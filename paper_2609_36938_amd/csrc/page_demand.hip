@@ -3,15 +3,22 @@
 // of selected, physically adjacent pages, split from the low end at max_run)
 // and the corrective-read set of Eq. (2) (actual minus predicted pages).
 //
-// Union: each block takes a contiguous range of query rows, maps every valid
-// id to its physical page and sets it in an LDS bitmap (read-before-set, so
-// the hot pages that every row selects cost one LDS read, not an atomic);
-// the block then ORs its non-empty words into the global bitmap.
-// Runs and lists: one 1024-thread block stages the bitmap in LDS (at most
-// 64 KB) and walks it there; each thread owns a
-// contiguous word range, and block-wide scans give it the page-list offset,
-// the run offset, the last unset page before its range (where the run it
-// starts in began) and the first unset page after it (where a run ends).
+// Union: each block takes a contiguous range of query rows, four rows' ids in
+// flight at a time, maps every valid id to its physical page and sets it in
+// an LDS bitmap (read-before-set, so the hot pages that every row selects cost
+// one LDS read, not an atomic; ids of one thread on one logical page, as
+// ascending selections have them, are looked up once); the block then ORs its
+// non-empty words into the global bitmap.
+// Lists and runs: a block stages the whole bitmap in LDS (at most 64 KB) and
+// emits a slice of RUN_THREADS words, one word per thread: what lies before
+// the slice (pages, run starts, the last unset page) it counts itself, so that
+// the slices need nothing from each other.
+// Few ids: one block does all of it, in one launch instead of three.
+//
+// What bounds all of these is latency: chains of loads and barriers, and the
+// launches.  Measured: the union of 4096 rows of 2048 ids 28 -> 10 us, of 64
+// rows 20 -> 5; list and runs of 2.1K pages 5 -> 4.2, of 81K pages 12 -> 10.4;
+// two rows in one launch 7.6 us instead of 1 + 7 + 12 in three.
 #include "janus_device.hpp"
 #include "janus_host.hpp"
 
@@ -19,8 +26,10 @@
 
 namespace janus {
 
-constexpr int PD_THREADS = 256;
+constexpr int PD_THREADS = 512;
 constexpr int PD_MAX_BLOCKS = 1024;
+constexpr int PD_ROWS = 4;          // rows in flight per block
+constexpr int PD_SMALL_IDS = 16384; // up to this many ids one block does everything
 constexpr int RUN_THREADS = 1024;
 constexpr int RUN_WAVES = RUN_THREADS / kWave;
 constexpr int PD_MAX_PAGES = 1 << 19;  // 64 KB LDS bitmap
@@ -32,37 +41,109 @@ __global__ void bitmap_zero(uint32_t *__restrict__ bm, int nwords)
         bm[w] = 0u;
 }
 
-__global__ __launch_bounds__(PD_THREADS) void page_union(
-    const int32_t *__restrict__ q_start, const int32_t *__restrict__ hist_len, int num_seqs, int es, int total_q,
-    const int32_t *__restrict__ topk_idx, int k, const int32_t *__restrict__ page_table, int pt_ld,
-    int page_shift, const int32_t *__restrict__ limit, int nwords, uint32_t *__restrict__ bitmap)
+struct UnionArgs {
+    const int32_t *q_start, *hist_len;
+    int num_seqs, es;
+    const int32_t *topk_idx;
+    int k, vec;  // vec: rows of ids may be read 16 bytes at a time
+    const int32_t *page_table;
+    int pt_ld, page_shift;
+    const int32_t *limit;
+};
+
+// Sets the pages of rows [r0, r1) in the LDS bitmap; T threads.
+template <int T>
+JANUS_DEV void union_rows(const UnionArgs &u, int r0, int r1, uint32_t *sbm)
+{
+    if (r0 >= r1)
+        return;
+    int b = __builtin_amdgcn_readfirstlane(session_of_row_wave(u.q_start, u.num_seqs, r0));
+    int next = u.q_start[b + 1];
+    // the session's id limit and page table
+    auto limit_of = [&](int s, int begin, int end) {
+        const int ctx = entries_of(u.hist_len[s] + (end - begin), u.es);
+        return min(ctx, u.limit ? u.limit[s] : entries_of(u.hist_len[s], u.es));
+    };
+    int lim = limit_of(b, u.q_start[b], next);
+    const int32_t *pt = u.page_table + (int64_t)b * u.pt_ld;
+    for (int r = r0; r < r1; r += PD_ROWS) {
+        int lims[PD_ROWS];
+        const int32_t *pts[PD_ROWS];
+#pragma unroll
+        for (int i = 0; i < PD_ROWS; ++i) {
+            lims[i] = 0;  // rows past the end select nothing
+            pts[i] = pt;
+            if (r + i < r1) {
+                if (r + i >= next) {
+                    while (r + i >= next) {
+                        ++b;
+                        next = u.q_start[b + 1];
+                    }
+                    lim = limit_of(b, u.q_start[b], next);
+                    pt = u.page_table + (int64_t)b * u.pt_ld;
+                }
+                lims[i] = lim;
+                pts[i] = pt;
+            }
+        }
+        for (int j0 = 0; j0 < u.k; j0 += 4 * T) {
+            // this thread's four ids of each row: consecutive ones, or T apart
+            v4i id[PD_ROWS];
+            const int j = u.vec ? j0 + 4 * (int)threadIdx.x : j0 + (int)threadIdx.x;
+#pragma unroll
+            for (int i = 0; i < PD_ROWS; ++i) {
+                id[i] = v4i{-1, -1, -1, -1};
+                const int32_t *row = u.topk_idx + (int64_t)(r + i) * u.k;
+                if (r + i < r1) {
+                    if (u.vec) {
+                        if (j < u.k)
+                            id[i] = *(const v4i *)(row + j);
+                    } else {
+#pragma unroll
+                        for (int c = 0; c < 4; ++c)
+                            if (j + c * T < u.k)
+                                id[i][c] = row[j + c * T];
+                    }
+                }
+            }
+            int page[PD_ROWS][4];
+#pragma unroll
+            for (int i = 0; i < PD_ROWS; ++i)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const int s = id[i][c];
+                    page[i][c] = -1;
+                    const bool dup = c > 0 && id[i][c > 0 ? c - 1 : 0] >= 0 && id[i][c > 0 ? c - 1 : 0] < lims[i] &&
+                                     (id[i][c > 0 ? c - 1 : 0] >> u.page_shift) == (s >> u.page_shift);
+                    if (s >= 0 && s < lims[i] && !dup)
+                        page[i][c] = pts[i][s >> u.page_shift];
+                }
+#pragma unroll
+            for (int i = 0; i < PD_ROWS; ++i)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const int p = page[i][c];
+                    if (p >= 0) {
+                        const uint32_t bit = 1u << (p & 31);
+                        if (!(sbm[p >> 5] & bit))
+                            atomicOr(&sbm[p >> 5], bit);
+                    }
+                }
+        }
+    }
+}
+
+__global__ __launch_bounds__(PD_THREADS) void page_union(UnionArgs u, int total_q, int nwords,
+                                                         uint32_t *__restrict__ bitmap)
 {
     extern __shared__ uint32_t sbm[];
     for (int w = threadIdx.x; w < nwords; w += PD_THREADS)
         sbm[w] = 0u;
-    __syncthreads();
+    lds_sync();
     const int rows_per = (total_q + gridDim.x - 1) / gridDim.x;
-    const int r0 = blockIdx.x * rows_per;
-    const int r1 = min(total_q, r0 + rows_per);
-    int b = r0 < total_q ? session_of_row(q_start, num_seqs, r0) : 0;
-    for (int r = r0; r < r1; ++r) {
-        while (r >= q_start[b + 1])
-            ++b;
-        const int ctx = entries_of(hist_len[b] + (q_start[b + 1] - q_start[b]), es);
-        const int lim = min(ctx, limit ? limit[b] : entries_of(hist_len[b], es));
-        const int32_t *row = topk_idx + (int64_t)r * k;
-        const int32_t *pt = page_table + (int64_t)b * pt_ld;
-        for (int j = threadIdx.x; j < k; j += PD_THREADS) {
-            const int s = row[j];
-            if (s < 0 || s >= lim)
-                continue;
-            const int p = pt[s >> page_shift];
-            const uint32_t bit = 1u << (p & 31);
-            if (!(sbm[p >> 5] & bit))
-                atomicOr(&sbm[p >> 5], bit);
-        }
-    }
-    __syncthreads();
+    const int r0 = min(total_q, (int)blockIdx.x * rows_per);
+    union_rows<PD_THREADS>(u, r0, min(total_q, r0 + rows_per), sbm);
+    lds_sync();
     for (int w = threadIdx.x; w < nwords; w += PD_THREADS) {
         const uint32_t v = sbm[w];
         if (v && (__atomic_load_n(&bitmap[w], __ATOMIC_RELAXED) & v) != v)
@@ -71,147 +152,189 @@ __global__ __launch_bounds__(PD_THREADS) void page_union(
 }
 
 struct RunShared {
-    int32_t wi[RUN_WAVES];
-    int32_t wx[RUN_WAVES];
-    int32_t wn[RUN_WAVES];
+    int32_t a[RUN_WAVES], b[RUN_WAVES], c[RUN_WAVES], d[RUN_WAVES];
+    int32_t fz[RUN_THREADS];  // first unset page from thread t's words on
 };
 
-// Block-wide exclusive scans over RUN_THREADS threads: sum, max, and a min
-// over the threads after this one.
-JANUS_DEV void run_scans(RunShared &sh, int cnt, int lastzero, int firstzero, int &cnt_excl, int &tot,
-                         int &lz_before, int &fz_after)
+JANUS_DEV int op_add(int a, int b) { return a + b; }
+JANUS_DEV int op_max(int a, int b) { return max(a, b); }
+JANUS_DEV int op_min(int a, int b) { return min(a, b); }
+
+// Block-wide inclusive scans of two values over RUN_THREADS threads, with
+// their totals and one barrier; s, t: one scratch value per wave each, free
+// until the next barrier after this call.  before_a: a's scan over the threads
+// before this one.
+template <class OpA, class OpB>
+JANUS_DEV void run_scan2(int32_t *s, int32_t *t, int &a, int unit_a, OpA op_a, int &b, int unit_b, OpB op_b,
+                         int &before_a, int &total_a, int &total_b)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int s = cnt, mx = lastzero, mn = firstzero;
+    const int wave = threadIdx.x >> 6;
+    const int ia = wave_scan(a, unit_a, op_a), ib = wave_scan(b, unit_b, op_b);
+    if ((threadIdx.x & 63) == 63) {
+        s[wave] = ia;
+        t[wave] = ib;
+    }
+    lds_sync();
+    int ba = unit_a, bb = unit_b;
+    total_a = unit_a;
+    total_b = unit_b;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        int t = __shfl_up(s, o, 64);
-        int u = __shfl_up(mx, o, 64);
-        int v = __shfl_down(mn, o, 64);
-        if (lane >= o) {
-            s += t;
-            mx = max(mx, u);
-        }
-        if (lane + o < 64)
-            mn = min(mn, v);
-    }
-    if (lane == 63) {
-        sh.wi[wave] = s;
-        sh.wx[wave] = mx;
-    }
-    if (lane == 0)
-        sh.wn[wave] = mn;
-    __syncthreads();
-    int off = 0, mxo = -1, mno = 0x7fffffff, t = 0;
     for (int w = 0; w < RUN_WAVES; ++w) {
-        t += sh.wi[w];
-        if (w < wave) {
-            off += sh.wi[w];
-            mxo = max(mxo, sh.wx[w]);
-        }
-        if (w > wave)
-            mno = min(mno, sh.wn[w]);
+        const int x = s[w], y = t[w];
+        ba = w < wave ? op_a(ba, x) : ba;
+        bb = w < wave ? op_b(bb, y) : bb;
+        total_a = op_a(total_a, x);
+        total_b = op_b(total_b, y);
     }
-    __syncthreads();
-    // exclusive versions: remove this thread's own contribution
-    const int incl_s = s + off;
-    cnt_excl = incl_s - cnt;
-    tot = t;
-    int mx_excl = __shfl_up(mx, 1, 64);
-    if (lane == 0)
-        mx_excl = -1;
-    lz_before = max(mx_excl, mxo);
-    int mn_excl = __shfl_down(mn, 1, 64);
-    if (lane == 63)
-        mn_excl = 0x7fffffff;
-    fz_after = min(mn_excl, mno);
+    before_a = op_a(ba, dpp_move<0x138, 0xf>(unit_a, ia));  // lane - 1's scan (none in lane 0)
+    a = op_a(ba, ia);
+    b = op_b(bb, ib);
 }
 
-// Walks the pages of `words` (nbits valid bits): writes the ascending page
-// list (if list != NULL), the packed runs, and the two counts.
-template <class Words>
-JANUS_DEV void emit_list_runs(RunShared &sh, Words words, int nbits, int max_run, int32_t *list,
-                              int32_t *runs, int32_t *n_pages_out, int32_t *n_runs_out)
+// Run starts among the pages of word w (bits v), and their pieces emitted: a
+// maximal run of set pages is cut from its low end into pieces of max_run.
+// last_zero: the last unset page before the word; first_zero(w): the first
+// unset page after word w.
+template <class FirstZero, class Emit>
+JANUS_DEV int run_starts(int w, uint32_t v, int last_zero, int max_run, FirstZero first_zero, Emit emit)
 {
-    const int nwords = (nbits + 31) >> 5;
-    const int wpt = (nwords + RUN_THREADS - 1) / RUN_THREADS;
-    const int w0 = min(nwords, threadIdx.x * wpt), w1 = min(nwords, w0 + wpt);
-    auto word = [&](int w) -> uint32_t {
-        uint32_t v = words(w);
-        const int hi = nbits - (w << 5);
-        if (hi < 32)
-            v &= (1u << hi) - 1u;
-        return v;
-    };
-    // this range: set pages, last and first unset page
-    int npages = 0, lastzero = -1, firstzero = 0x7fffffff;
-    for (int w = w0; w < w1; ++w) {
-        const uint32_t v = word(w);
-        npages += __popc(v);
-        if (v != 0xffffffffu) {
-            if (firstzero == 0x7fffffff)
-                firstzero = (w << 5) + __ffs(~v) - 1;
-            lastzero = (w << 5) + 31 - __clz(~v);
+    int n = 0;
+    while (v) {
+        const int i = __ffs(v) - 1;
+        const uint32_t rest = ~(v >> i);
+        const int len = rest ? __ffs(rest) - 1 : 32;  // set pages from i on (at most 32 - i: zeros are shifted in)
+        const int lo = (w << 5) + i, hi = lo + min(len, 32 - i);
+        // the first piece that starts at or after lo: lo itself, unless the run began before this word
+        int skip = 0;
+        if (i == 0 && last_zero != lo - 1) {
+            const int m = (lo - last_zero - 1) % max_run;
+            skip = m ? max_run - m : 0;
         }
-    }
-    int page_off, total_pages, lz_before, fz_after;
-    run_scans(sh, npages, lastzero, firstzero, page_off, total_pages, lz_before, fz_after);
-    const int end_zero = min(fz_after, nbits);  // first unset page after this range (or nbits)
-    // first walk: count run starts
-    auto walk = [&](bool emit, int run_pos) -> int {
-        int nstart = 0;
-        int prev = (w0 << 5) - 1;
-        // (p - start of p's run) mod max_run, carried from page to page; the
-        // first page of this range may continue a run that began before it
-        int rem = -1;
-        int pos = page_off;
-        for (int w = w0; w < w1; ++w) {
-            uint32_t v = word(w);
-            while (v) {
-                const int p = (w << 5) + __ffs(v) - 1;
-                v &= v - 1u;
-                if (p != prev + 1)
-                    rem = 0;
-                else if (rem < 0)
-                    rem = (p - (lz_before + 1)) % max_run;
-                else
-                    rem = rem + 1 == max_run ? 0 : rem + 1;
-                prev = p;
-                if (emit && list)
-                    list[pos++] = p;
-                if (rem == 0) {
-                    if (emit) {
-                        // run ends at the first unset page after p
-                        int ez = end_zero;
-                        for (int w2 = p >> 5; w2 < w1; ++w2) {
-                            uint32_t z = ~word(w2);
-                            if (w2 == (p >> 5))  // only pages above p
-                                z &= ~((2u << (p & 31)) - 1u);
-                            if (z) {
-                                ez = (w2 << 5) + __ffs(z) - 1;
-                                break;
-                            }
-                        }
-                        if (ez > nbits)
-                            ez = nbits;
-                        runs[2 * (run_pos + nstart)] = p;
-                        runs[2 * (run_pos + nstart) + 1] = min(max_run, ez - p);
-                    }
-                    ++nstart;
-                }
+        if (skip < hi - lo) {
+            for (int p = lo + skip;; p += max_run) {
+                emit(n, p, hi);
+                ++n;
+                if (max_run >= hi - p)
+                    break;
             }
         }
-        return nstart;
-    };
-    const int nstart = walk(false, 0);
-    int run_off, total_runs, d0, d1;
-    run_scans(sh, nstart, -1, 0x7fffffff, run_off, total_runs, d0, d1);
-    walk(true, run_off);
-    if (threadIdx.x == 0) {
-        if (n_pages_out)
-            *n_pages_out = total_pages;
-        *n_runs_out = total_runs;
+        if (i + len >= 32)
+            break;
+        v &= ~0u << (i + len);
     }
+    return n;
+}
+
+// Run starts among the pages of word w: run_starts' count.  With max_run >= 32
+// a word's runs have one start each, but the one that began before the word,
+// which has one at most.
+template <class FirstZero>
+JANUS_DEV int count_starts(int w, uint32_t v, int last_zero, int max_run, FirstZero first_zero)
+{
+    if (max_run < 32)
+        return run_starts(w, v, last_zero, max_run, first_zero, [](int, int, int) {});
+    int n = __popc(v & ~(v << 1));
+    if ((v & 1u) && last_zero != (w << 5) - 1) {
+        const int len = ~v ? __ffs(~v) - 1 : 32, m = ((w << 5) - last_zero - 1) % max_run;
+        n -= m != 0 && max_run - m >= len ? 1 : 0;
+    }
+    return n;
+}
+
+// Walks the pages of the bitmap sw in LDS (nbits bits, zeros past them; whole
+// 32-bit words): writes, for this block's slice of RUN_THREADS words, one per
+// thread, the ascending page list (if list != NULL) and the packed runs, and in
+// the first block the two counts.
+JANUS_DEV void emit_list_runs(RunShared &sh, const uint32_t *sw, int nbits, int max_run, int32_t *list, int32_t *runs,
+                              int32_t *n_pages_out, int32_t *n_runs_out)
+{
+    const int nwords = (nbits + 31) >> 5, tid = threadIdx.x;
+    const int wpt = max(1, (nwords + RUN_THREADS - 1) / RUN_THREADS);  // words of a thread's range
+    auto last_unset = [&](int w, uint32_t v) { return (w << 5) + 31 - __clz((int)~v); };  // v not all ones
+    // over ranges of wpt words: the first unset page from each range on
+    // (ranges taken from the end), the last one before each
+    int before;
+    {
+        const int t = RUN_THREADS - 1 - tid, e0 = min(nwords, t * wpt), e1 = min(nwords, e0 + wpt);
+        int fz = nbits, lz = -1, tf, tl;
+        for (int w = e1 - 1; w >= e0; --w)
+            if (sw[w] != 0xffffffffu)
+                fz = min(nbits, (w << 5) + __ffs(~sw[w]) - 1);
+        const int a0 = min(nwords, tid * wpt), a1 = min(nwords, a0 + wpt);
+        for (int w = a0; w < a1; ++w)
+            if (sw[w] != 0xffffffffu)
+                lz = last_unset(w, sw[w]);
+        run_scan2(sh.a, sh.b, lz, -1, op_max, fz, nbits, op_min, before, tl, tf);
+        sh.fz[t] = fz;
+    }
+    // the first unset page after word w
+    auto first_zero = [&](int w) {
+        for (int x = w + 1; x < nwords; ++x) {
+            if (wpt == 1 || x % wpt == 0)  // a range's first word
+                return sh.fz[wpt == 1 ? x : x / wpt];
+            if (sw[x] != 0xffffffffu)
+                return min(nbits, (x << 5) + __ffs(~sw[x]) - 1);
+        }
+        return nbits;
+    };
+    // one slice, and what lies before it: nothing, or counted here
+    const int s0 = blockIdx.x * RUN_THREADS, w = s0 + tid;
+    const uint32_t v = w < nwords ? sw[w] : 0u;
+    int pages_before = 0, starts_before = 0, lb = before, unused;
+    if (wpt > 1) {
+        int pages = 0, starts = 0, L = before, zl = -1, zero_before, one = 0;
+        const int a0 = min(nwords, tid * wpt), a1 = min(nwords, a0 + wpt);
+        for (int x = a0; x < a1; ++x) {
+            const uint32_t y = sw[x];
+            if (s0 == 0 || x < s0) {  // (the first block counts everything, for the totals)
+                pages += __popc(y);
+                starts += count_starts(x, y, L, max_run, first_zero);
+            }
+            if (y != 0xffffffffu) {
+                L = last_unset(x, y);
+                if (x < s0)
+                    zl = L;
+            }
+        }
+        run_scan2(sh.c, sh.d, pages, 0, op_add, starts, 0, op_add, unused, pages_before, starts_before);
+        run_scan2(sh.a, sh.b, zl, -1, op_max, one, 0, op_add, unused, zero_before, unused);
+        if (s0 == 0) {
+            if (tid == 0) {
+                if (n_pages_out)
+                    *n_pages_out = pages_before;
+                *n_runs_out = starts_before;
+            }
+            pages_before = starts_before = 0;
+        }
+        int z = w < nwords && v != 0xffffffffu ? last_unset(w, v) : -1;
+        run_scan2(sh.c, sh.d, z, -1, op_max, one, 0, op_add, lb, unused, unused);
+        lb = max(lb, zero_before);
+    }
+    int np = __popc(v), ns = count_starts(w, v, lb, max_run, first_zero), tp, ts, pages_at;
+    const int own_starts = ns;
+    run_scan2(wpt > 1 ? sh.a : sh.c, wpt > 1 ? sh.b : sh.d, np, 0, op_add, ns, 0, op_add, pages_at, tp, ts);
+    if (wpt == 1 && s0 == 0 && tid == 0) {
+        if (n_pages_out)
+            *n_pages_out = tp;
+        *n_runs_out = ts;
+    }
+    int pos = pages_before + pages_at;
+    const int rpos = starts_before + ns - own_starts;
+    if (list)
+        for (uint32_t x = v; x; x &= x - 1u)
+            list[pos++] = (w << 5) + __ffs(x) - 1;
+    if (own_starts)
+        run_starts(w, v, lb, max_run, first_zero, [&](int n, int p, int hi) {
+            const int end = (hi & 31) == 0 ? first_zero(w) : hi;  // a run up to the word's end may go on
+            *(v2i *)(runs + 2 * (int64_t)(rpos + n)) = v2i{p, min(max_run, end - p)};
+        });
+}
+
+// The bitmap's words, with zeros past nbits
+JANUS_DEV uint32_t masked_word(const uint32_t *bm, int w, int nbits)
+{
+    const int hi = nbits - (w << 5);
+    return hi < 32 ? bm[w] & ((1u << hi) - 1u) : bm[w];
 }
 
 __global__ __launch_bounds__(RUN_THREADS) void page_list_runs(const uint32_t *__restrict__ bitmap, int nbits,
@@ -222,9 +345,29 @@ __global__ __launch_bounds__(RUN_THREADS) void page_list_runs(const uint32_t *__
     extern __shared__ uint32_t sw[];  // the bitmap's words
     const int nwords = (nbits + 31) >> 5;
     for (int w = threadIdx.x; w < nwords; w += RUN_THREADS)
-        sw[w] = bitmap[w];
-    __syncthreads();
-    emit_list_runs(sh, [&](int w) { return sw[w]; }, nbits, max_run, list, runs, counts, counts + 1);
+        sw[w] = masked_word(bitmap, w, nbits);
+    lds_sync();
+    emit_list_runs(sh, sw, nbits, max_run, list, runs, counts, counts + 1);
+}
+
+// All of page demand in one block
+__global__ __launch_bounds__(RUN_THREADS) void page_demand_small(UnionArgs u, int total_q, int nbits, int max_run,
+                                                                 uint32_t *__restrict__ bitmap,
+                                                                 int32_t *__restrict__ list,
+                                                                 int32_t *__restrict__ runs,
+                                                                 int32_t *__restrict__ counts)
+{
+    __shared__ RunShared sh;
+    extern __shared__ uint32_t sw[];
+    const int nwords = (nbits + 31) >> 5;
+    for (int w = threadIdx.x; w < nwords; w += RUN_THREADS)
+        sw[w] = 0u;
+    lds_sync();
+    union_rows<RUN_THREADS>(u, 0, total_q, sw);
+    lds_sync();
+    for (int w = threadIdx.x; w < nwords; w += RUN_THREADS)
+        bitmap[w] = sw[w];
+    emit_list_runs(sh, sw, nbits, max_run, list, runs, counts, counts + 1);
 }
 
 __global__ __launch_bounds__(RUN_THREADS) void predict_diff_kernel(
@@ -232,54 +375,39 @@ __global__ __launch_bounds__(RUN_THREADS) void predict_diff_kernel(
     uint32_t *__restrict__ miss, int32_t *__restrict__ miss_runs, int32_t *__restrict__ counts)
 {
     __shared__ RunShared sh;
-    __shared__ int32_t red[3][RUN_WAVES];
     extern __shared__ uint32_t sw[];  // the miss set's words
     const int nwords = (nbits + 31) >> 5;
     int ca = 0, cp = 0, cap = 0;
     for (int w = threadIdx.x; w < nwords; w += RUN_THREADS) {
-        uint32_t a = actual[w], p = predicted[w];
-        const int hi = nbits - (w << 5);
-        if (hi < 32) {
-            a &= (1u << hi) - 1u;
-            p &= (1u << hi) - 1u;
-        }
+        const uint32_t a = masked_word(actual, w, nbits), p = masked_word(predicted, w, nbits);
         ca += __popc(a);
         cp += __popc(p);
         cap += __popc(a & p);
-        miss[w] = a & ~p;
         sw[w] = a & ~p;
+        if (blockIdx.x == 0)
+            miss[w] = a & ~p;
     }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        ca += __shfl_xor(ca, o, 64);
-        cp += __shfl_xor(cp, o, 64);
-        cap += __shfl_xor(cap, o, 64);
-    }
-    if (lane == 0) {
-        red[0][wave] = ca;
-        red[1][wave] = cp;
-        red[2][wave] = cap;
-    }
-    __syncthreads();  // also orders the staged miss words before the run walk reads them
-    if (threadIdx.x == 0) {
-        int a = 0, p = 0, ap = 0;
-        for (int w = 0; w < RUN_WAVES; ++w) {
-            a += red[0][w];
-            p += red[1][w];
-            ap += red[2][w];
+    if (blockIdx.x == 0) {
+        int na, np, nap, unused, one = 0;
+        run_scan2(sh.a, sh.b, ca, 0, op_add, cp, 0, op_add, unused, na, np);
+        run_scan2(sh.c, sh.d, cap, 0, op_add, one, 0, op_add, unused, nap, unused);
+        if (threadIdx.x == 0) {
+            counts[0] = na;
+            counts[1] = np;
+            counts[2] = nap;
+            counts[3] = na - nap;
         }
-        counts[0] = a;
-        counts[1] = p;
-        counts[2] = ap;
-        counts[3] = a - ap;
     }
-    emit_list_runs(sh, [&](int w) { return sw[w]; }, nbits, max_run, nullptr, miss_runs, nullptr, counts + 4);
+    lds_sync();  // the staged words are read from here on
+    emit_list_runs(sh, sw, nbits, max_run, nullptr, miss_runs, nullptr, counts + 4);
 }
 
 } // namespace janus
 
 using namespace janus;
+
+// Blocks of the list and run kernels: one per slice of words
+static int run_blocks(int nwords) { return std::max(1, ceil_div(nwords, RUN_THREADS)); }
 
 extern "C" int janus_page_demand(const janus_batch *bt, const int32_t *topk_idx, int k,
                                  const int32_t *page_table, int pt_ld, int page_size, const int32_t *limit,
@@ -297,20 +425,24 @@ extern "C" int janus_page_demand(const janus_batch *bt, const int32_t *topk_idx,
         return JANUS_ERR_UNSUPPORTED;
     hipStream_t st = as_stream(stream);
     const int nwords = (num_phys_pages + 31) >> 5;
+    const size_t lds = std::max(nwords, 1) * sizeof(uint32_t);
+    const int vec = k % 4 == 0 && (reinterpret_cast<uintptr_t>(topk_idx) & 15) == 0;
+    const UnionArgs u = {bt->q_start, bt->hist_len, bt->num_seqs, bt->entry_shift, topk_idx, k, vec, page_table,
+                         pt_ld, __builtin_ctz((unsigned)page_size), limit};
+    // one block looks up an id about as fast as the launches it saves take
+    // for PD_SMALL_IDS of them
+    if (bt->total_q > 0 && nwords > 0 && (int64_t)bt->total_q * k <= PD_SMALL_IDS && nwords <= RUN_THREADS) {
+        hipLaunchKernelGGL(page_demand_small, dim3(1), dim3(RUN_THREADS), lds, st, u, (int)bt->total_q,
+                           num_phys_pages, max_run, bitmap, page_list, runs, counts);
+        return launch_status();
+    }
     if (nwords > 0)
         hipLaunchKernelGGL(bitmap_zero, dim3(ceil_div(nwords, 256)), dim3(256), 0, st, bitmap, nwords);
-    if (bt->total_q > 0 && nwords > 0) {
-        const int64_t entries = (int64_t)bt->total_q * k;
-        const int nblk = (int)std::min<int64_t>(std::min<int64_t>(PD_MAX_BLOCKS, bt->total_q),
-                                                std::max<int64_t>(1, entries / (PD_THREADS * 16)));
-        const int shift = __builtin_ctz((unsigned)page_size);
-        hipLaunchKernelGGL(page_union, dim3(nblk), dim3(PD_THREADS), nwords * sizeof(uint32_t), st, bt->q_start,
-                           bt->hist_len, bt->num_seqs, bt->entry_shift, bt->total_q, topk_idx, k, page_table, pt_ld,
-                           shift, limit,
-                           nwords, bitmap);
-    }
-    hipLaunchKernelGGL(page_list_runs, dim3(1), dim3(RUN_THREADS), std::max(nwords, 1) * sizeof(uint32_t), st, bitmap,
-                       num_phys_pages, max_run, page_list, runs, counts);
+    if (bt->total_q > 0 && nwords > 0)
+        hipLaunchKernelGGL(page_union, dim3(std::min<int>(PD_MAX_BLOCKS, bt->total_q)), dim3(PD_THREADS), lds, st, u,
+                           (int)bt->total_q, nwords, bitmap);
+    hipLaunchKernelGGL(page_list_runs, dim3(run_blocks(nwords)), dim3(RUN_THREADS), lds, st, bitmap, num_phys_pages,
+                       max_run, page_list, runs, counts);
     return launch_status();
 }
 
@@ -322,7 +454,8 @@ extern "C" int janus_predict_diff(const uint32_t *actual, const uint32_t *predic
     if (num_phys_pages > PD_MAX_PAGES)
         return JANUS_ERR_UNSUPPORTED;
     const int nwords = (num_phys_pages + 31) >> 5;
-    hipLaunchKernelGGL(predict_diff_kernel, dim3(1), dim3(RUN_THREADS), std::max(nwords, 1) * sizeof(uint32_t),
-                       as_stream(stream), actual, predicted, num_phys_pages, max_run, miss, miss_runs, counts);
+    hipLaunchKernelGGL(predict_diff_kernel, dim3(run_blocks(nwords)), dim3(RUN_THREADS),
+                       std::max(nwords, 1) * sizeof(uint32_t), as_stream(stream), actual, predicted, num_phys_pages,
+                       max_run, miss, miss_runs, counts);
     return launch_status();
 }

@@ -72,15 +72,6 @@ struct alignas(16) TopkShared {
     float thr_f;       // thr_key as a score (the same test on floats)
 };
 
-// Workgroup barrier that orders LDS only.  __syncthreads() also waits for
-// every outstanding global load.
-JANUS_DEV void lds_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // Score of an order-preserving key (inverse of score_key).  Keys below that of
 // -inf are not scores; they map to -inf, which only makes a threshold looser.
 JANUS_DEV float key_score(uint32_t key)

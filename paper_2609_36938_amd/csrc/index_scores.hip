@@ -1065,7 +1065,7 @@ __global__ __launch_bounds__(256, 4) void index_scores_general(
 namespace janus {
 
 // Row-tile kernel: a block takes up to NQ tokens of one session and one
-// chunk of 1024, 2048 or 4096 keys (chosen per launch).  It serves
+// chunk of 256 to 4096 keys (chosen per launch).  It serves
 // decode-shaped batches (every session appends at most NQ tokens, as in the
 // decode phase: the scores are a GEMV over each session's keys, bound by
 // reading the keys once), with fp8 or MXFP4 keys.  The four waves take the
@@ -1080,27 +1080,58 @@ namespace janus {
 // group: one 256-byte store per token and group; groups wholly past every
 // token's causal limit skip the MFMAs (their stores write -inf).
 constexpr int ROWS_NQ = 4;
-constexpr int ROWS_CHUNK_MAX = 4096;   // keys per block: 4096, 2048 or 1024
-constexpr int ROWS_CHUNK_MIN = 1024;
+constexpr int ROWS_CHUNK_MAX = 4096;   // keys per block: 4096, 2048, .. 256
+constexpr int ROWS_CHUNK_MIN = 256;
+constexpr int ROWS_CHUNK_GRID = 1024;  // the chunk that a launch's grid is checked for; shorter ones only where they fit
+constexpr int ROWS_BLOCK_KEYS = 128;   // what a block costs besides its keys, in keys
+
+// Block -> (session, first key): the session's lane holds the block's number
+// in the wave's prefix sums of chunk counts (chunk = 2^shift), 64 sessions a
+// step.  Scalar results; b = -1 past the last block.
+JANUS_DEV void rows_block(const int32_t *ctx_start, int num_seqs, int shift, int block, int &b, int &c0)
+{
+    int left = block, s0 = 0;  // blocks of this step's sessions and later ones
+    for (;;) {
+        const int s = s0 + (int)(threadIdx.x & 63);
+        const int n = s < num_seqs ? (ctx_start[s + 1] - ctx_start[s] + (1 << shift) - 1) >> shift : 0;
+        const int incl = wave_sum_scan(n);
+        const uint64_t past = __ballot(incl > left);
+        const int l = past ? __builtin_ctzll(past) : 63;
+        const int upto = __builtin_amdgcn_readlane(incl, l);
+        b = past ? s0 + l : -1;
+        c0 = (left - (upto - __builtin_amdgcn_readlane(n, l))) << shift;
+        left -= upto;
+        s0 += kWave;
+        if (past || s0 >= num_seqs)
+            break;
+    }
+}
 
 template <int NQ, bool FP4>
 __global__ __launch_bounds__(256, 2) void index_scores_rows(
     const int32_t *__restrict__ q_start, const int32_t *__restrict__ ctx_start,
     const int32_t *__restrict__ hist_len, const int64_t *__restrict__ score_start, int num_seqs, int es, int nchunks,
-    int chunk, int one_tile, const uint8_t *__restrict__ q, const float *__restrict__ q_scale, const uint8_t *__restrict__ kI,
+    int chunk, const uint8_t *__restrict__ q, const float *__restrict__ q_scale, const uint8_t *__restrict__ kI,
     const uint8_t *__restrict__ k_bscale, const float *__restrict__ k_scale, const float *__restrict__ w,
     float *__restrict__ scores)
 {
-    // block = (tile, chunk), chunk fastest; with one tile per session the
-    // tile is the session
-    const int tile = blockIdx.x / nchunks;
-    const int c0 = (blockIdx.x - tile * nchunks) * chunk;
-    int b = tile, t0 = 0;
-    if (!one_tile && !tile_slot(q_start, num_seqs, tile, NQ, b, t0))
-        return;
+    // one token per session: blocks numbered session by session, chunk by
+    // chunk (a grid of the longest session's chunks for each was nearly half
+    // empty blocks); more tokens: that grid, chunk fastest (behind the search
+    // the compiler needs more registers than these instances have)
+    int b, c0;
+    if constexpr (NQ == 1) {
+        rows_block(ctx_start, num_seqs, 31 - __builtin_clz(chunk), (int)blockIdx.x, b, c0);
+        if (b < 0)
+            return;
+    } else {
+        b = blockIdx.x / nchunks;
+        c0 = (blockIdx.x - b * nchunks) * chunk;
+    }
+    constexpr int t0 = 0;
     const int qs = q_start[b], N = q_start[b + 1] - qs;
     const int M = hist_len[b], ctx = entries_of(M + N, es);
-    const int nv = min(NQ, N - t0);  // tokens of this tile
+    const int nv = min(NQ, N);  // tokens of this session
     if (nv <= 0 || c0 >= ctx)
         return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1292,26 +1323,35 @@ static int prefill_chunks(const janus_batch *bt)
     return IDX_XCD * std::max(1, ceil_div(ceil_div(bt->max_ctx, IDX_XCD), IDX_KEY_CHUNK));
 }
 
-// Tiles of the row-tile kernel: one per session when no session appends
-// more than NQ tokens, else an upper bound (ceil(total_q / NQ) + sessions).
-static int64_t rows_tiles(const janus_batch *bt, int nq)
-{
-    return bt->max_q <= nq ? bt->num_seqs : ceil_div(bt->total_q, nq) + (int64_t)bt->num_seqs;
-}
+// The row-tile kernel serves sessions of at most ROWS_NQ appended tokens, one
+// tile of them each.
 static int rows_nq(const janus_batch *bt) { return bt->max_q <= 1 ? 1 : bt->max_q <= 2 ? 2 : ROWS_NQ; }
+// (the bound that decides which batches it takes: a grid of the longest
+// session's 1024-key chunks for each tile of ROWS_NQ tokens)
 static bool rows_grid_ok(const janus_batch *bt)
 {
-    return rows_tiles(bt, rows_nq(bt)) * ceil_div(bt->max_ctx, ROWS_CHUNK_MIN) <= INT32_MAX;
+    const int nq = rows_nq(bt);
+    const int64_t tiles =
+        bt->max_q <= nq ? bt->num_seqs : ceil_div(bt->total_q, nq) + (int64_t)bt->num_seqs;
+    return tiles * ceil_div(bt->max_ctx, ROWS_CHUNK_GRID) <= INT32_MAX;
+}
+// Blocks of a launch.  One token per session: at most this many chunks (every
+// session's last one may be partial); else the longest session's for each.
+static int64_t rows_blocks(const janus_batch *bt, int chunk)
+{
+    return rows_nq(bt) == 1 ? bt->total_ctx / chunk + bt->num_seqs
+                            : (int64_t)bt->num_seqs * ceil_div(bt->max_ctx, chunk);
 }
 
-// Keys per block.  A ragged batch's blocks fill the GPU's resident block
-// slots in rounds, the last one part-empty, and few blocks leave CUs idle:
-// of 4096, 2048 and 1024 keys, take the chunk whose estimated block count
-// fills its rounds best (ties, within 5%, go to the longer chunk, which
-// loads its tokens' queries once for more keys).  A session of C keys makes
-// about C/chunk + 1/2 blocks per tile.
+// Keys per block, 4096 down to 256 (one 64-key group per wave).  The blocks
+// run in rounds of the GPU's resident block slots, each as long as a chunk and
+// what a block pays besides (loading its tokens' queries, about as long as
+// ROWS_BLOCK_KEYS more keys): take the chunk with the shortest total.  A full
+// batch (5M keys in 64 sessions) gets 1024 keys, a small one the shortest:
+// two sessions of 28K keys in all took 21 us as 8 blocks of 4096 keys, and
+// 6 as 109 of 256.  A session of C keys makes about C/chunk + 1/2 blocks.
 template <typename Kern>
-static int rows_chunk(const janus_batch *bt, int64_t tiles, Kern kern)
+static int rows_chunk(const janus_batch *bt, Kern kern)
 {
     int dev = 0, cus = 0, per = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
@@ -1319,34 +1359,31 @@ static int rows_chunk(const janus_batch *bt, int64_t tiles, Kern kern)
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, 256, 0) != hipSuccess || cus < 1 || per < 1)
         return ROWS_CHUNK_MAX;
     const double slots = (double)per * cus;
-    const double tiles_per_seq = (double)tiles / bt->num_seqs;
     int best = ROWS_CHUNK_MAX;
-    double best_fill = -1.0;
+    double best_cost = 0.0;
     for (int c = ROWS_CHUNK_MAX; c >= ROWS_CHUNK_MIN; c /= 2) {
-        const double blocks = tiles_per_seq * ((double)bt->total_ctx / c + 0.5 * bt->num_seqs);
-        const double fill = blocks / (std::ceil(blocks / slots) * slots);
-        if (fill > best_fill + 0.05) {
-            best_fill = fill;
+        if (c < ROWS_CHUNK_GRID && rows_blocks(bt, c) > (1 << 24) - 1)
+            break;  // a launch takes fewer than 2^32 threads
+        const double blocks = (double)bt->total_ctx / c + 0.5 * bt->num_seqs;
+        const double cost = std::ceil(blocks / slots) * (c + ROWS_BLOCK_KEYS);
+        if (c == ROWS_CHUNK_MAX || cost < best_cost) {
+            best_cost = cost;
             best = c;
         }
     }
     return best;
 }
 
-// 1-D grid of the row-tile kernel: (tile, key chunk), chunk fastest
 template <bool FP4>
 static void launch_rows(const janus_batch *bt, const void *q, const float *q_scale, const void *kI,
                         const uint8_t *k_bscale, const float *k_scale, const float *w, float *scores, hipStream_t st)
 {
     const int nq = rows_nq(bt);
-    const int one_tile = bt->max_q <= nq;
-    const int64_t tiles = rows_tiles(bt, nq);
     auto go = [&](auto kern) {
-        const int chunk = rows_chunk(bt, tiles, kern);
-        const int nchunks = ceil_div(bt->max_ctx, chunk);
-        hipLaunchKernelGGL(kern, dim3((unsigned)(tiles * nchunks)), dim3(256), 0, st, bt->q_start, bt->ctx_start,
-                           bt->hist_len, bt->score_start, bt->num_seqs, bt->entry_shift, nchunks, chunk, one_tile,
-                           (const uint8_t *)q, q_scale, (const uint8_t *)kI, k_bscale, k_scale, w, scores);
+        const int chunk = rows_chunk(bt, kern);
+        hipLaunchKernelGGL(kern, dim3((unsigned)rows_blocks(bt, chunk)), dim3(256), 0, st, bt->q_start, bt->ctx_start,
+                           bt->hist_len, bt->score_start, bt->num_seqs, bt->entry_shift,
+                           ceil_div(bt->max_ctx, chunk), chunk, (const uint8_t *)q, q_scale, (const uint8_t *)kI, k_bscale, k_scale, w, scores);
     };
     if (nq == 1)
         go(index_scores_rows<1, FP4>);

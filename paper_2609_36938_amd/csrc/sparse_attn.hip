@@ -894,37 +894,38 @@ __global__ __launch_bounds__(64 * NW, 1) void sparse_mla_mfma(
 // 32-key tiles fills the CU's LDS, would run one wave per 16 heads through
 // each tile's chain of phases: one to four waves per CU.  Here HB head blocks
 // x NG key groups run as HB * NG waves: wave (hb, group) holds the queries of
-// head block hb, takes the 16-key tiles T = group, group + NG, ... and keeps
+// head block hb, takes the KT-key tiles T = group, group + NG, ... and keeps
 // its own softmax state and all 512 output dims (128 registers), so that no P
 // is exchanged and only the hand-over of a tile shared by a group's waves
 // needs a barrier (none with one head block).  The groups are merged once per
-// row, through LDS.  A group's ring has RING tiles of 18 KB; NG * RING = 8
-// tiles and the slots fill the 160 KB.  P V runs on the 16-key MFMA at half
-// its 32-key rate: MFMA time is not what bounds these head counts, and a
-// 32-key tile would halve the groups.  Measured at 2048 rows x 2048 ids of a
-// 64K history: 16 heads 1793 -> 448 us (10.8 TB/s of logical gather), 32
-// heads 1323 -> 497, 64 heads 1158 -> 864.  With 128 heads the waves' own
-// reads of V (each all of it) would bound the kernel; the kernel above shares
-// them.
+// row, through LDS.  A group's ring has RING tiles; all of them and the slots
+// fill the 160 KB.  16 and 32 heads take four groups of 16-key tiles, whose
+// P V runs on the 16-key MFMA at half its 32-key rate: MFMA time does not
+// bound them.  64 heads take two groups of 32-key tiles (864 us with the
+// former).  With 128 heads the waves' own reads of K and V (each all of them)
+// would bound the kernel (1239 us against 1107): the kernel above shares V.
+// Measured at 2048 rows x 2048 ids of a 64K history, against one to four waves
+// per CU: 16 heads 1793 -> 446 us (10.8 TB/s of logical gather), 32 heads 1323
+// -> 515, 64 heads 1158 -> 686.
 //
 // Tile layout: dims 0..511 of row r (1 KB) at 1024 r, 16-byte chunk c at slot
 // c ^ few_swz(r): the 16 rows of a K operand read fall in 16 different
 // 16-byte bank groups, and the 8 rows x 32 bytes of half a transposing V read
-// too.  Dims 512..575 follow in two 1 KB blocks of eight rows, laid out as
-// the kernel above lays out its tail blocks.
-constexpr int FEW_KT = 16;
-constexpr int FEW_TAIL = FEW_KT * 1024;
-constexpr int FEW_TILEB = FEW_TAIL + 2 * 1024;
-constexpr int FEW_TILES = 8;       // tile buffers per block
-constexpr int FEW_DIMS = 128;      // output dims per merge round
+// too.  Dims 512..575 follow in 1 KB blocks of eight rows, laid out as the
+// kernel above lays out its tail blocks.
+constexpr int FEW_RING_BYTES = 8 * 16 * 1152;  // all tile buffers of a block
+constexpr int FEW_DIMS = 128;            // output dims per merge round
 constexpr int FEW_PITCH = FEW_DIMS + 4;  // floats per head in a merge round (the four lane groups' rows in distinct banks)
 template <int HB>
 constexpr int few_groups() { return HB == 4 ? 2 : 4; }
-JANUS_DEV int few_swz(int r) { return ((r << 1) & 15) | (r >> 3); }
+template <int HB>
+constexpr int few_kt() { return HB == 4 ? 32 : 16; }
+JANUS_DEV int few_swz(int r) { return ((r << 1) & 15) | ((r >> 3) & 1); }
+// chunk cc (dims 512 + 8cc ..) of row r in the tail blocks
 JANUS_DEV int few_tail(int r, int cc)
 {
     const int m = r >> 3;
-    return FEW_TAIL + 1024 * m + 16 * (8 * (cc ^ m) + ((r & 7) ^ cc));
+    return 1024 * m + 16 * (8 * (cc ^ (m & 1)) + ((r & 7) ^ cc));
 }
 
 // 16 bytes per lane from a wave-uniform row (byte offset off per lane) into
@@ -949,10 +950,13 @@ __global__ __launch_bounds__(512, 2) void sparse_mla_few(
     int k, float scale_log2, void *__restrict__ out, int out_f32, float *__restrict__ lse, int num_splits,
     float *__restrict__ part)
 {
-    constexpr int NG = few_groups<HB>(), RING = FEW_TILES / NG, NW = HB * NG, NT = 64 * NW, HQ = 16 * HB;
-    constexpr int ROWS = FEW_KT / HB;          // main rows a wave gathers per tile
-    constexpr int NTAIL = HB == 1 ? 2 : 1;     // tail blocks (waves hb < 2)
-    __shared__ __attribute__((aligned(16))) uint8_t sTile[FEW_TILES * FEW_TILEB];
+    constexpr int NG = few_groups<HB>(), NW = HB * NG, NT = 64 * NW, HQ = 16 * HB;
+    constexpr int KT = few_kt<HB>(), KB = KT / 16, TILEB = KT * 1152, TAIL = KT * 1024;
+    constexpr int RING = FEW_RING_BYTES / (NG * TILEB);
+    constexpr int ROWS = KT / HB;                           // main rows a wave gathers per tile
+    constexpr int TAILS = KT / 8, NTAIL = (TAILS + HB - 1) / HB;  // tail blocks, and a wave's (of the first TAILS waves)
+    static_assert(RING >= 2 && RING * NG * TILEB == FEW_RING_BYTES, "the tiles fill the ring");
+    __shared__ __attribute__((aligned(16))) uint8_t sTile[FEW_RING_BYTES];
     __shared__ int32_t sSlot[MLA_MAX_K];
     const int g = SPLIT ? blockIdx.x / num_splits : blockIdx.x;
     int kl = k;
@@ -989,9 +993,10 @@ __global__ __launch_bounds__(512, 2) void sparse_mla_few(
     for (int nb = 0; nb < MLA_NB; ++nb)
         o[nb] = v4f{0.f, 0.f, 0.f, 0.f};
     float m = M_INIT, lsum = 0.f;  // head c16 of the block
-    const int ntiles = (kl + FEW_KT - 1) / FEW_KT;
+    const int ntiles = (kl + KT - 1) / KT;
     const int nsteps = (ntiles + NG - 1) / NG;
-    uint8_t *ring = sTile + grp_k * RING * FEW_TILEB;
+    uint8_t *ring = sTile + grp_k * RING * TILEB;
+    const bool has_tail = hb < TAILS;
 
     // this wave's share of the gather of its group's tile at step s (a tile
     // past the selection gathers row 0, so that the counts stay fixed)
@@ -1007,32 +1012,32 @@ __global__ __launch_bounds__(512, 2) void sparse_mla_few(
     struct Slots {
         int main, tail[NTAIL];
     };
-    // slots of step s: lane l holds row l % 16's, and tail[u] the one of the
-    // row that this lane loads in a tail block: lane l fills slot
-    // l = 8*(cc ^ mb) + (i ^ cc) of block mb with chunk cc of row 8*mb + i
+    // slots of step s: lane l holds row l % KT's, and tail[u] the one of the
+    // row that this lane loads in tail block mb: lane l fills slot
+    // l = 8*(cc ^ (mb & 1)) + (i ^ cc) of the block with chunk cc of row 8*mb + i
+    auto tail_block = [&](int u) { return HB >= TAILS ? hb % TAILS : NTAIL * hb + u; };
     auto read_slots = [&](int s, Slots &v) {
-        const int k0 = FEW_KT * (s * NG + grp_k), ln = lane_copy();
-        int x = sSlot[min(k0 + (ln & 15), kl - 1)];
-        v.main = k0 + (ln & 15) < kl ? max(x, 0) : 0;  // padding rows read a real row; their logits are masked
+        const int k0 = KT * (s * NG + grp_k), ln = lane_copy(), r = ln & (KT - 1);
+        int x = sSlot[min(k0 + r, kl - 1)];
+        v.main = k0 + r < kl ? max(x, 0) : 0;  // padding rows read a real row; their logits are masked
 #pragma unroll
         for (int u = 0; u < NTAIL; ++u) {
-            const int mb = HB == 1 ? u : (hb & 1), cc = (ln >> 3) ^ mb, r = 8 * mb + ((ln & 7) ^ cc);
-            x = sSlot[min(k0 + r, kl - 1)];
-            v.tail[u] = k0 + r < kl ? max(x, 0) : 0;
+            const int mb = tail_block(u), cc = (ln >> 3) ^ (mb & 1), rt = 8 * mb + ((ln & 7) ^ cc);
+            x = sSlot[min(k0 + rt, kl - 1)];
+            v.tail[u] = k0 + rt < kl ? max(x, 0) : 0;
         }
     };
     auto fire_main = [&](int s, int i, const Slots &v) {
         const int r = ROWS * hb + i;
         const uint32_t sl = (uint32_t)__builtin_amdgcn_readlane(v.main, r);
         gather16_row(kv + (uint64_t)sl * rb, (16u * lane_copy()) ^ (16u * few_swz(r)),
-                     ring_lds + (uint32_t)((s % RING) * FEW_TILEB + 1024 * r));
+                     ring_lds + (uint32_t)((s % RING) * TILEB + 1024 * r));
     };
     auto fire_tail = [&](int s, int u, const Slots &v) {
-        if (HB > 2 && hb >= 2)
+        if (!has_tail)
             return;
-        const int mb = HB == 1 ? u : (hb & 1), cc = (lane_copy() >> 3) ^ mb;
-        gather16(kv + (uint64_t)(uint32_t)v.tail[u] * rb + 16 * (64 + cc),
-                 ring + (s % RING) * FEW_TILEB + FEW_TAIL + 1024 * mb);
+        const int mb = tail_block(u), cc = (lane_copy() >> 3) ^ (mb & 1);
+        gather16(kv + (uint64_t)(uint32_t)v.tail[u] * rb + 16 * (64 + cc), ring + (s % RING) * TILEB + TAIL + 1024 * mb);
     };
     auto issue = [&](int s) {
         Slots v;
@@ -1047,58 +1052,63 @@ __global__ __launch_bounds__(512, 2) void sparse_mla_few(
     // this wave's gathers have landed up to those of the newest `pend` steps
     auto wait_steps = [&](int pend) {
         constexpr int IPW = ROWS + NTAIL;
-        const bool tail = HB <= 2 || hb < 2;
         if (pend <= 0)
             __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
         else if (pend == 1)
-            tail ? __builtin_amdgcn_s_waitcnt(vmcnt_only(IPW)) : __builtin_amdgcn_s_waitcnt(vmcnt_only(ROWS));
+            has_tail ? __builtin_amdgcn_s_waitcnt(vmcnt_only(IPW)) : __builtin_amdgcn_s_waitcnt(vmcnt_only(ROWS));
         else
-            tail ? __builtin_amdgcn_s_waitcnt(vmcnt_only(2 * IPW)) : __builtin_amdgcn_s_waitcnt(vmcnt_only(2 * ROWS));
+            has_tail ? __builtin_amdgcn_s_waitcnt(vmcnt_only(2 * IPW)) : __builtin_amdgcn_s_waitcnt(vmcnt_only(2 * ROWS));
     };
-    // K operands in flight ahead of their MFMA, and V operands read before
-    // the softmax (one wave per SIMD has the registers for all of K)
-    constexpr int KAHEAD = 4, VAHEAD = 8;
+    // K operands in flight ahead of their MFMA, and V operands read before the softmax
+    constexpr int KAHEAD = 4 / KB + 1, VAHEAD = 8 / KB;
     // computes step s; with NEXT, step s + RING - 1's gathers go out among its MFMAs
     auto compute = [&](int s, auto nextc) {
         constexpr bool NEXT = decltype(nextc)::value;
-        const int k0 = FEW_KT * (s * NG + grp_k), sn = s + RING - 1;
-        const uint8_t *tile = ring + (s % RING) * FEW_TILEB;
+        const int k0 = KT * (s * NG + grp_k), sn = s + RING - 1;
+        const uint8_t *tile = ring + (s % RING) * TILEB;
         Slots nv;
         if constexpr (NEXT)
             read_slots(sn, nv);
         const int ln = lane_copy(), lc = ln & 15, lg = ln >> 4;
-        const int vslot = sSlot[min(k0 + lc, kl - 1)];
-        // K operand of K-step st: row lc, chunk 4*st + lg; V operand of dims
-        // 16*nb ..: row 4*lg + lc/4, dims 16*nb + 4*(lc%4) ..  Both walk the
-        // swizzled chunks so that one address serves four reads: the n-th
+        const int vslot = sSlot[min(k0 + (ln & (KT - 1)), kl - 1)];
+        // K operand of K-step st: row lc (+ 16 kb), chunk 4*st + lg; V operand of
+        // dims 16*nb ..: row 4*lg + lc/4 (+ 16 kb), dims 16*nb + 4*(lc%4) ..  Both
+        // walk the swizzled chunks so that one address serves four steps: the n-th
         // K-step is st = 4*(n%4) + n/4, the n-th V block nb = 8*(n%4) + n/4
         const int kaddr = 1024 * lc + 16 * (lg ^ few_swz(lc));
-        auto kop = [&](int n) {
-            const int off = n < 16 ? (kaddr ^ (64 * (n >> 2))) + 256 * (n & 3) : few_tail(lc, 4 * (n - 16) + lg);
+        auto kop = [&](int n, int kb) {
+            const int off = n < 16 ? (kaddr ^ (64 * (n >> 2))) + 256 * (n & 3) + 16384 * kb
+                                   : TAIL + few_tail(lc, 4 * (n - 16) + lg) + 2048 * kb;
             return as_v8bf(*(const v4i *)(tile + off));
         };
         const int vr0 = 4 * lg + (lc >> 2);
         const int vaddr = 1024 * vr0 + 16 * (((lc >> 1) & 1) ^ few_swz(vr0)) + 8 * (lc & 1);
-        auto vop = [&](int n) { return lds_read_tr16(tile, (vaddr ^ (32 * (n >> 2))) + 256 * (n & 3)); };
-        // S^T[key 4*grp + i][head c16] in two chains
-        v4f s0 = v4f{0.f, 0.f, 0.f, 0.f}, s1 = s0;
-        v8bf kr[KAHEAD];
+        auto vop = [&](int n, int kb) {
+            return lds_read_tr16(tile, (vaddr ^ (32 * (n >> 2))) + 256 * (n & 3) + 16384 * kb);
+        };
+        // S^T[key 16*kb + 4*grp + i][head c16]: one chain per key block, two for one block
+        v4f sc[2] = {v4f{0.f, 0.f, 0.f, 0.f}, v4f{0.f, 0.f, 0.f, 0.f}};
+        v8bf kr[KAHEAD][KB];
 #pragma unroll
         for (int n = 0; n < KAHEAD; ++n)
-            kr[n] = kop(n);
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb)
+                kr[n][kb] = kop(n, kb);
 #pragma unroll
         for (int n = 0; n < MLA_STEPS; ++n) {
             const int st = n < 16 ? 4 * (n & 3) + (n >> 2) : n;
-            if (n & 1)
-                s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kr[n % KAHEAD], qf[st], s1, 0, 0, 0);
-            else
-                s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kr[n % KAHEAD], qf[st], s0, 0, 0, 0);
-            if (n + KAHEAD < MLA_STEPS)
-                kr[n % KAHEAD] = kop(n + KAHEAD);
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) {
+                const int ch = KB == 1 ? (n & 1) : kb;
+                sc[ch] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kr[n % KAHEAD][kb], qf[st], sc[ch], 0, 0, 0);
+                if (n + KAHEAD < MLA_STEPS)
+                    kr[n % KAHEAD][kb] = kop(n + KAHEAD, kb);
+            }
             if constexpr (NEXT) {
-                // ROWS main gathers from the second K-step on, the tails at the end
-                if (n >= 1 && n <= 16 && (n - 1) % HB == 0)
-                    fire_main(sn, (n - 1) / HB, nv);
+                // ROWS main gathers spread from the second K-step on, the tails at the end
+                constexpr int EVERY = 16 / ROWS;
+                if (n >= 1 && n <= 16 && (n - 1) % EVERY == 0)
+                    fire_main(sn, (n - 1) / EVERY, nv);
                 if (n == 17)
 #pragma unroll
                     for (int u = 0; u < NTAIL; ++u)
@@ -1106,16 +1116,28 @@ __global__ __launch_bounds__(512, 2) void sparse_mla_few(
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        v4s16 vr[VAHEAD];
+        v4s16 vr[VAHEAD][KB];
 #pragma unroll
         for (int n = 0; n < VAHEAD; ++n)
-            vr[n] = vop(n);
-        const uint32_t vmask = (uint32_t)__ballot(k0 + lc < kl && vslot >= 0) >> (4 * lg);
-        float x[4], mx = -INFINITY;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            x[i] = ((vmask >> i) & 1u) ? (s0[i] + s1[i]) * scale_log2 : -INFINITY;
-            mx = fmaxf(mx, x[i]);
+            for (int kb = 0; kb < KB; ++kb)
+                vr[n][kb] = vop(n, kb);
+        if constexpr (KB == 1)
+            sc[0] += sc[1];
+        // a tile of valid keys (every one but a row's last, when the scale is
+        // positive) takes its max over the raw products and one fma per probability
+        const uint32_t vbits = (uint32_t)__ballot(k0 + (ln & (KT - 1)) < kl && vslot >= 0);
+        const bool fast = KB == 2 && vbits == 0xFFFFFFFFu && scale_log2 > 0.f;
+        float x[4 * KB], mx = -INFINITY;
+        if (fast) {
+            mx = scale_log2 * max8(sc[0], sc[1]);
+        } else {
+            const uint32_t vmask = vbits >> (4 * (lane_here() >> 4));
+#pragma unroll
+            for (int e = 0; e < 4 * KB; ++e) {
+                x[e] = ((vmask >> (16 * (e >> 2) + (e & 3))) & 1u) ? sc[e >> 2][e & 3] * scale_log2 : -INFINITY;
+                mx = fmaxf(mx, x[e]);
+            }
         }
         // the running max moves (for all four lane groups of a head) only when a logit exceeds it by the slack
         if (__ballot(mx > m + RESCALE_SLACK) != 0) {
@@ -1139,20 +1161,38 @@ __global__ __launch_bounds__(512, 2) void sparse_mla_few(
                 for (int i = 0; i < 4; ++i)
                     o[nb][i] *= ai[i];
         }
-        float p[4];
+        float p[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        if (fast) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            p[i] = __builtin_amdgcn_exp2f(x[i] - m);
-            lsum += p[i];
+            for (int e = 0; e < 4 * KB; ++e)
+                p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[e >> 2][e & 3], scale_log2, -m));
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4 * KB; ++e)
+                p[e] = __builtin_amdgcn_exp2f(x[e] - m);
         }
-        typedef __bf16 v4bf __attribute__((ext_vector_type(4)));
-        const v4s16 pa = __builtin_bit_cast(v4s16, (v4bf{(__bf16)p[0], (__bf16)p[1], (__bf16)p[2], (__bf16)p[3]}));
+#pragma unroll
+        for (int e = 0; e < 4 * KB; ++e)
+            lsum += p[e];
+        const v8bf pa = v8bf{(__bf16)p[0], (__bf16)p[1], (__bf16)p[2], (__bf16)p[3],
+                             (__bf16)p[4], (__bf16)p[5], (__bf16)p[6], (__bf16)p[7]};
+        const v8s16 ps = __builtin_bit_cast(v8s16, pa);
+        const v4s16 pa_lo = v4s16{ps[0], ps[1], ps[2], ps[3]};
+        auto both = [](v4s16 lo, v4s16 hi) {
+            return __builtin_bit_cast(v8bf, (v8s16){lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]});
+        };
 #pragma unroll
         for (int n = 0; n < MLA_NB; ++n) {
             const int nb = 8 * (n & 3) + (n >> 2);
-            o[nb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pa, vr[n % VAHEAD], o[nb], 0, 0, 0);
+            if constexpr (KB == 1)
+                o[nb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pa_lo, vr[n % VAHEAD][0], o[nb], 0, 0, 0);
+            else
+                o[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    pa, both(vr[n % VAHEAD][0], vr[n % VAHEAD][KB - 1]), o[nb], 0, 0, 0);
             if (n + VAHEAD < MLA_NB)
-                vr[n % VAHEAD] = vop(n + VAHEAD);
+#pragma unroll
+                for (int kb = 0; kb < KB; ++kb)
+                    vr[n % VAHEAD][kb] = vop(n + VAHEAD, kb);
             __builtin_amdgcn_sched_barrier(0);
         }
     };

@@ -52,6 +52,51 @@ constexpr float RESCALE_SLACK = 8.0f;           // log2 headroom before O is res
 constexpr float M_INIT = -3.0e38f;
 
 typedef short v4s16 __attribute__((ext_vector_type(4)));
+typedef __bf16 v4bf __attribute__((ext_vector_type(4)));
+
+// Four consecutive outputs at element `at` of out (fp32, or rounded to bf16),
+// in one store whatever out's alignment.
+typedef v4f v4f_any __attribute__((aligned(4)));
+typedef v2i v2i_any __attribute__((aligned(2)));
+JANUS_DEV void store_out4(void *out, int out_f32, int64_t at, v4f v)
+{
+    if (out_f32)
+        *(v4f_any *)((float *)out + at) = v;
+    else
+        *(v2i_any *)((uint16_t *)out + at) = __builtin_bit_cast(v2i, __builtin_convertvector(v, v4bf));
+}
+
+// The pool rows of the kl <= U * T ids at sel, in LDS (-1: padding); T threads.
+// In two halves, with the query loads between them: loads come back in order,
+// so the ids must go out before the queries and their page table entries
+// after, and all of a thread's at once (one id at a time they were a chain of
+// dependent loads: 16 heads 443 -> 410 us; the 128-head kernel, whose eight
+// waves share four ids each, was no faster for it).
+template <int T, int U>
+struct SlotMap {
+    int s[U];
+    JANUS_DEV void load(const int32_t *sel, int kl)
+    {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = (int)threadIdx.x + u * T;
+            s[u] = j < kl ? sel[j] : -1;
+        }
+    }
+    JANUS_DEV void map(int kl, int lim, const int32_t *pt, int page_shift, int32_t *slots)
+    {
+        int p[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            p[u] = s[u] >= 0 && s[u] <= lim ? pt[s[u] >> page_shift] : 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = (int)threadIdx.x + u * T;
+            if (j < kl)
+                slots[j] = s[u] >= 0 && s[u] <= lim ? (p[u] << page_shift) + (s[u] & ((1 << page_shift) - 1)) : -1;
+        }
+    }
+};
 
 // s_waitcnt immediate (gfx9 encoding) that waits for vmcnt <= n only.
 constexpr int vmcnt_only(int n) { return (n & 15) | ((n >> 4) << 14) | (7 << 4) | (15 << 8); }
@@ -905,8 +950,8 @@ __global__ __launch_bounds__(64 * NW, 1) void sparse_mla_mfma(
 // former).  With 128 heads the waves' own reads of K and V (each all of them)
 // would bound the kernel (1239 us against 1107): the kernel above shares V.
 // Measured at 2048 rows x 2048 ids of a 64K history, against one to four waves
-// per CU: 16 heads 1793 -> 446 us (10.8 TB/s of logical gather), 32 heads 1323
-// -> 515, 64 heads 1158 -> 686.
+// per CU: 16 heads 1793 -> 410 us (11.8 TB/s of logical gather), 32 heads 1323
+// -> 501, 64 heads 1158 -> 679.
 //
 // Tile layout: dims 0..511 of row r (1 KB) at 1024 r, 16-byte chunk c at slot
 // c ^ few_swz(r): the 16 rows of a K operand read fall in 16 different
@@ -968,17 +1013,14 @@ __global__ __launch_bounds__(512, 2) void sparse_mla_few(
         kl = min(k, j0 + tps * MLA_KT) - j0;
         sel += j0;
     }
-    const int b = session_of_row(q_start, num_seqs, g);
+    const int b = __builtin_amdgcn_readfirstlane(session_of_row_wave(q_start, num_seqs, g));
     const int lim = last_cand(hist_len[b], g - q_start[b], es);
     const int32_t *pt = page_table + (int64_t)b * pt_ld;
-    const int psz_mask = (1 << page_shift) - 1;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int hb = wave % HB, grp_k = wave / HB;  // head block, key group
     const int c16 = lane & 15, grp = lane >> 4;
-    for (int j = tid; j < kl; j += NT) {
-        const int s = sel[j];
-        sSlot[j] = (s >= 0 && s <= lim) ? ((pt[s >> page_shift] << page_shift) + (s & psz_mask)) : -1;
-    }
+    SlotMap<NT, MLA_MAX_K / NT> ids;
+    ids.load(sel, kl);
     // queries of head 16*hb + c16, dims 32*st + 8*grp .. +7
     v8bf qf[MLA_STEPS];
     {
@@ -987,7 +1029,8 @@ __global__ __launch_bounds__(512, 2) void sparse_mla_few(
         for (int st = 0; st < MLA_STEPS; ++st)
             qf[st] = as_v8bf(*(const v4i *)(qr + 32 * st));
     }
-    // O for heads 4*grp + i of the block over dims 16*nb + c16
+    ids.map(kl, lim, pt, page_shift, sSlot);
+    // O^T for head c16 of the block over dims 16*nb + 4*grp + i
     v4f o[MLA_NB];
 #pragma unroll
     for (int nb = 0; nb < MLA_NB; ++nb)
@@ -1151,15 +1194,11 @@ __global__ __launch_bounds__(512, 2) void sparse_mla_few(
             const float alpha = __builtin_amdgcn_exp2f(m - mnew);
             lsum *= alpha;
             m = mnew;
-            float ai[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                ai[i] = from(4 * (lr >> 4) + i, alpha);
 #pragma unroll
             for (int nb = 0; nb < MLA_NB; ++nb)
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    o[nb][i] *= ai[i];
+                    o[nb][i] *= alpha;
         }
         float p[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         if (fast) {
@@ -1185,10 +1224,10 @@ __global__ __launch_bounds__(512, 2) void sparse_mla_few(
         for (int n = 0; n < MLA_NB; ++n) {
             const int nb = 8 * (n & 3) + (n >> 2);
             if constexpr (KB == 1)
-                o[nb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pa_lo, vr[n % VAHEAD][0], o[nb], 0, 0, 0);
+                o[nb] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vr[n % VAHEAD][0], pa_lo, o[nb], 0, 0, 0);
             else
                 o[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                    pa, both(vr[n % VAHEAD][0], vr[n % VAHEAD][KB - 1]), o[nb], 0, 0, 0);
+                    both(vr[n % VAHEAD][0], vr[n % VAHEAD][KB - 1]), pa, o[nb], 0, 0, 0);
             if (n + VAHEAD < MLA_NB)
 #pragma unroll
                 for (int kb = 0; kb < KB; ++kb)
@@ -1242,16 +1281,11 @@ __global__ __launch_bounds__(512, 2) void sparse_mla_few(
         sL[16 * wave + c16] = lsum;
     }
     __syncthreads();
-    float f[4];
+    float f = sM[16 * hb + c16];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int h = 4 * grp + i;
-        float mg = sM[16 * hb + h];
-#pragma unroll
-        for (int gk = 1; gk < NG; ++gk)
-            mg = fmaxf(mg, sM[16 * (gk * HB + hb) + h]);
-        f[i] = __builtin_amdgcn_exp2f(sM[16 * wave + h] - mg);
-    }
+    for (int gk = 1; gk < NG; ++gk)
+        f = fmaxf(f, sM[16 * (gk * HB + hb) + c16]);
+    f = __builtin_amdgcn_exp2f(m - f);
     if (tid < HQ) {  // head tid: 16*(tid/16) + tid%16
         float mg = sM[tid], l = 0.f;
 #pragma unroll
@@ -1271,15 +1305,12 @@ __global__ __launch_bounds__(512, 2) void sparse_mla_few(
                 lse[(int64_t)g * HQ + tid] = l > 0.f ? (mg + log2f(l)) * LN2 : -INFINITY;
         }
     }
-    const bool wide = (reinterpret_cast<uintptr_t>(out) & 15) == 0;
 #pragma unroll
     for (int r = 0; r < MLA_DV / FEW_DIMS; ++r) {
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < FEW_DIMS / 16; ++j)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                sO[(16 * wave + 4 * grp + i) * FEW_PITCH + 16 * j + c16] = o[r * (FEW_DIMS / 16) + j][i] * f[i];
+            *(v4f *)(sO + (16 * wave + c16) * FEW_PITCH + 16 * j + 4 * grp) = o[r * (FEW_DIMS / 16) + j] * f;
         __syncthreads();
         for (int e = tid; e < HQ * (FEW_DIMS / 4); e += NT) {
             const int h = e / (FEW_DIMS / 4), d4 = e % (FEW_DIMS / 4);
@@ -1292,28 +1323,7 @@ __global__ __launch_bounds__(512, 2) void sparse_mla_few(
             if constexpr (SPLIT) {
                 *(v4f *)(part + ((int64_t)blockIdx.x * HQ + h) * MLA_DV + d) = a;
             } else {
-                const int64_t at = ((int64_t)g * HQ + h) * MLA_DV + d;
-                if (out_f32) {
-                    float *dst = (float *)out + at;
-                    if (wide)
-                        *(v4f *)dst = a;
-                    else
-#pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            dst[i] = a[i];
-                } else {
-                    uint16_t *dst = (uint16_t *)out + at;
-                    const uint16_t h0 = f32_to_bf16_rne(a[0]), h1 = f32_to_bf16_rne(a[1]), h2 = f32_to_bf16_rne(a[2]),
-                                   h3 = f32_to_bf16_rne(a[3]);
-                    if (wide) {
-                        *(v2i *)dst = v2i{(int)(h0 | ((uint32_t)h1 << 16)), (int)(h2 | ((uint32_t)h3 << 16))};
-                    } else {
-                        dst[0] = h0;
-                        dst[1] = h1;
-                        dst[2] = h2;
-                        dst[3] = h3;
-                    }
-                }
+                store_out4(out, out_f32, ((int64_t)g * HQ + h) * MLA_DV + d, a);
             }
         }
     }

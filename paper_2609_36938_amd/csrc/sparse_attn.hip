@@ -1347,6 +1347,11 @@ constexpr int MQA_TILEB = MLA_KT * MQA_ROWB;   // one 32-row tile (8 KB)
 constexpr int MQA_MAX_K = 1024;                // selected ids per token held in LDS
 constexpr int MQA_WAVES = 4;                   // tokens per block
 
+// SHARED: the four waves share one token, wave w taking tiles w, w + 4, .., and
+// are merged through LDS at the end, so that a quarter of a token's tiles run
+// in series instead of all of them; a block then serves one token instead of
+// four, and a block fills a CU's LDS (mqa_shared weighs the two).
+template <bool SHARED>
 __global__ __launch_bounds__(64 * MQA_WAVES, 1) void sparse_mqa_mfma(
     const int32_t *__restrict__ q_start, const int32_t *__restrict__ hist_len, int num_seqs, int es, int total_q,
     const uint16_t *__restrict__ q, int Hq, const uint8_t *__restrict__ k_pool, const uint8_t *__restrict__ v_pool,
@@ -1363,9 +1368,11 @@ __global__ __launch_bounds__(64 * MQA_WAVES, 1) void sparse_mqa_mfma(
     __shared__ __attribute__((aligned(16))) uint8_t sV1[MQA_WAVES][MQA_TILEB];
     __shared__ int32_t sSlotW[MQA_WAVES][MQA_MAX_K];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int g = blockIdx.x * MQA_WAVES + wave;
+    const int g = SHARED ? blockIdx.x : blockIdx.x * MQA_WAVES + wave;
     if (g >= total_q)
         return;
+    constexpr int TS = SHARED ? MQA_WAVES : 1;  // tiles from one of this wave's to the next
+    const int t0 = SHARED ? wave : 0;           // and its first
     const int c16 = lane & 15, grp = lane >> 4;
     const int b = session_of_row(q_start, num_seqs, g);
     const int lim = last_cand(hist_len[b], g - q_start[b], es);
@@ -1373,9 +1380,13 @@ __global__ __launch_bounds__(64 * MQA_WAVES, 1) void sparse_mqa_mfma(
     const int32_t *sel = topk + (int64_t)g * k;
     const int psz_mask = (1 << page_shift) - 1;
     int32_t *slots = sSlotW[wave];
-    for (int j = lane; j < k; j += 64) {
-        const int s = sel[j];
-        slots[j] = (s >= 0 && s <= lim) ? ((pt[s >> page_shift] << page_shift) + (s & psz_mask)) : -1;
+    // (two of this wave's tiles per step)
+    for (int t = t0 + TS * (lane >> 5); MLA_KT * t < k; t += 2 * TS) {
+        const int j = MLA_KT * t + (lane & 31);
+        if (j < k) {
+            const int s = sel[j];
+            slots[j] = (s >= 0 && s <= lim) ? ((pt[s >> page_shift] << page_shift) + (s & psz_mask)) : -1;
+        }
     }
     // B operand of S^T = K Q^T: head c16, dims 32*st + 8*grp .. +7
     v8bf qf[4];
@@ -1412,16 +1423,16 @@ __global__ __launch_bounds__(64 * MQA_WAVES, 1) void sparse_mqa_mfma(
             gather16(vs, vd + 1024 * i);
         }
     };
-    if (ntiles > 0)
-        issue(0, sK0[wave], sV0[wave]);
+    if (t0 < ntiles)
+        issue(t0, sK0[wave], sV0[wave]);
     // one tile: its K and V tiles (kt, vt) and the buffers (kn, vn) that take
-    // tile t+1's gathers first (they held tile t-1, read in full by now).
+    // the next tile's gathers first (they held the one before, read in full by now).
     // All four are restrict-qualified, so that the reads of this tile are not
     // made to wait for those gathers.
     auto tile_step = [&](int t, const uint8_t *__restrict__ kt, const uint8_t *__restrict__ vt,
                          uint8_t *__restrict__ kn, uint8_t *__restrict__ vn) {
-        if (t + 1 < ntiles) {
-            issue(t + 1, kn, vn);
+        if (t + TS < ntiles) {
+            issue(t + TS, kn, vn);
             __builtin_amdgcn_s_waitcnt(vmcnt_only(16));  // tile t has landed
         } else {
             __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
@@ -1493,15 +1504,51 @@ __global__ __launch_bounds__(64 * MQA_WAVES, 1) void sparse_mqa_mfma(
             o[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa, bv, o[nb], 0, 0, 0);
         }
     };
-    // tile t in buffers t % 2 (the loop unrolled by two)
-    for (int t = 0; t < ntiles; t += 2) {
+    // this wave's tiles in its two buffers in turn (the loop unrolled by two)
+    for (int t = t0; t < ntiles; t += 2 * TS) {
         tile_step(t, sK0[wave], sV0[wave], sK1[wave], sV1[wave]);
-        if (t + 1 < ntiles)
-            tile_step(t + 1, sK1[wave], sV1[wave], sK0[wave], sV0[wave]);
+        if (t + TS < ntiles)
+            tile_step(t + TS, sK1[wave], sV1[wave], sK0[wave], sV0[wave]);
     }
     float l = lsum;
     l += __shfl_xor(l, 16, 64);
     l += __shfl_xor(l, 32, 64);
+    if constexpr (SHARED) {
+        // merge: O to this wave's first K buffer ([16][128] floats), m and l to
+        // the slots' array; every wave's tiles are read by the barrier
+        float *ml = (float *)slots;
+        __syncthreads();
+        if (grp == 0) {
+            ml[c16] = m;
+            ml[16 + c16] = l;
+        }
+        float *po = (float *)sK0[wave];
+#pragma unroll
+        for (int nb = 0; nb < 8; ++nb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                po[(4 * grp + i) * MQA_D + 16 * nb + c16] = o[nb][i];
+        __syncthreads();
+        for (int e = threadIdx.x; e < Hq * (MQA_D / 4); e += 64 * MQA_WAVES) {
+            const int h = e / (MQA_D / 4), d4 = e % (MQA_D / 4);
+            float M = -INFINITY, L = 0.f, f[MQA_WAVES];
+#pragma unroll
+            for (int w = 0; w < MQA_WAVES; ++w)
+                M = fmaxf(M, ((const float *)sSlotW[w])[h]);
+            v4f acc = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < MQA_WAVES; ++w) {
+                const float mw = ((const float *)sSlotW[w])[h];
+                f[w] = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - M);
+                L += f[w] * ((const float *)sSlotW[w])[16 + h];
+                acc += *(const v4f *)((const float *)sK0[w] + h * MQA_D + 4 * d4) * f[w];
+            }
+            store_out4(out, out_f32, ((int64_t)g * Hq + h) * MQA_D + 4 * d4, acc * (L > 0.f ? 1.f / L : 0.f));
+            if (d4 == 0 && lse)
+                lse[(int64_t)g * Hq + h] = L > 0.f ? (M + log2f(L)) * LN2 : -INFINITY;
+        }
+        return;
+    }
     const float inv = l > 0.f ? 1.f / l : 0.f;
     if (grp == 0 && c16 < Hq && lse)
         lse[(int64_t)g * Hq + c16] = l > 0.f ? (m + log2f(l)) * LN2 : -INFINITY;
@@ -1712,6 +1759,17 @@ static bool mqa_shape(const void *q, int Hq, int dqk, int dv, const void *k_pool
            (reinterpret_cast<uintptr_t>(q) & 15) == 0;
 }
 
+// Whether a block's waves share one token: the batch's time in rounds of one
+// block per CU (256 of them), from rounds measured at 8 heads, in ns: 8000 + 9 k
+// with one token per block (10.3 us at k = 256, 17.3 at 1024), 3900 + 50 k with
+// four (16.7 and 55.1).
+static bool mqa_shared(int total_q, int k)
+{
+    const int64_t one = (int64_t)ceil_div(total_q, 256) * (8000 + 9 * k);
+    const int64_t four = (int64_t)ceil_div(total_q, 256 * MQA_WAVES) * (3900 + 50 * k);
+    return one < four;
+}
+
 // one launch of the MLA kernel: splits blocks per token, each over one slice
 // of the selection (part = NULL: splits = 1, normalised output); pool rows
 // of row_bytes bytes, bf16 or (kv8) fp8 with an inline scale
@@ -1855,8 +1913,10 @@ extern "C" int janus_sparse_attn(const janus_batch *bt, const void *q, int Hq, i
         return launch_status();
     }
     if (mqa_shape(q, Hq, dqk, dv, k_pool, v_pool, k_row_stride, v_row_stride, k)) {
-        hipLaunchKernelGGL(sparse_mqa_mfma, dim3((bt->total_q + MQA_WAVES - 1) / MQA_WAVES), dim3(64 * MQA_WAVES), 0,
-                           st, bt->q_start, bt->hist_len, bt->num_seqs, bt->entry_shift, (int)bt->total_q,
+        const bool shared = mqa_shared(bt->total_q, k);
+        hipLaunchKernelGGL(shared ? sparse_mqa_mfma<true> : sparse_mqa_mfma<false>,
+                           dim3(shared ? bt->total_q : ceil_div(bt->total_q, MQA_WAVES)), dim3(64 * MQA_WAVES), 0, st,
+                           bt->q_start, bt->hist_len, bt->num_seqs, bt->entry_shift, (int)bt->total_q,
                            (const uint16_t *)q, Hq, (const uint8_t *)k_pool, (const uint8_t *)v_pool,
                            2 * k_row_stride, 2 * v_row_stride, page_table, pt_ld, shift, topk_idx, k, sl2, out, of32,
                            lse);

@@ -234,16 +234,24 @@ JANUS_DEV uint32_t best(SM &sm, const uint32_t (&key)[NI], const int32_t (&id)[N
                 sm.few_id[at] = id[i];
             }
         lds_sync();
+        // (one thread per entry: by their owners, a wave's entries one after
+        // another, a bin of 60 ties took 65 us)
+        if ((int)threadIdx.x < cnt) {
+            const uint32_t mk = sm.few_key[threadIdx.x];
+            const int32_t mi = sm.few_id[threadIdx.x];
+            int rank = 0;
+#pragma unroll 4
+            for (int j = 0; j < cnt; ++j)
+                rank += sm.few_key[j] > mk || (sm.few_key[j] == mk && sm.few_id[j] < mi);
+            if (rank == want - 1)
+                set_threshold(sm, mk, mi);
+        }
+        lds_sync();
+        const uint32_t T = sm.thr_key;
+        const int32_t I = sm.thr_id;
 #pragma unroll
         for (int i = 0; i < NI; ++i)
-            if ((in >> i) & 1u) {
-                int rank = 0;
-                for (int j = 0; j < cnt; ++j)
-                    rank += sm.few_key[j] > key[i] || (sm.few_key[j] == key[i] && sm.few_id[j] < id[i]);
-                win |= (rank < want ? 1u : 0u) << i;
-                if (rank == want - 1)
-                    set_threshold(sm, key[i], id[i]);
-            }
+            win |= (((in >> i) & 1u) && (key[i] > T || (key[i] == T && id[i] <= I)) ? 1u : 0u) << i;
     } else {
         // many ties on one key: its smallest ids, the largest of ~id
         uint32_t inv[NI], ilo = 0xffffffffu, ihi = 0u;

@@ -18,11 +18,12 @@ SIZES = [(1, 1, 1), (64, 2, 64), (2048, 3, 2048), (4094, 4, 2048), (4099, 2, 100
          (16383, 2, 2047), (40000, 2, 4000), (262200, 1, 2048)]
 
 
-@pytest.mark.parametrize("fill", list(FILLS))
-@pytest.mark.parametrize("hist,new,k", SIZES)
+# (the longest row: one order, one tie-heavy and one usual fill)
+CASES = [(f, *s) for s in SIZES for f in FILLS if s[0] < 200000 or f in ("hot", "descending", "few_levels")]
+
+
+@pytest.mark.parametrize("fill,hist,new,k", CASES)
 def test_topk_edges(fill, hist, new, k):
-    if hist > 200000 and fill not in ("hot", "descending", "few_levels"):
-        pytest.skip("one order, one tie-heavy and one usual fill of the longest row")
     rng = np.random.default_rng(7)
     ctx = hist + new
     rows = np.full((new, ctx), -np.inf, np.float32)

@@ -5,9 +5,11 @@
 // One block per row.  A row (up to 557 KB at a 128K history) does not fit in
 // LDS, so the block streams it from HBM once, keeping only candidates that
 // beat a running threshold in an LDS buffer of CAP (key, id) pairs:
-//   1. threshold seed: a strided sample of whole 128-byte lines (1/32 of a
-//      128K row) gives the key of a rank a little above k * (sample share), so
-//      that in expectation ~1.3k elements pass;
+//   1. threshold seed: a strided sample of 8-element groups (1/32 of a 128K
+//      row) gives the key of a rank a little above k * (sample share), so that
+//      in expectation ~1.3k elements pass.  (Whole 128-byte lines, four times as
+//      far apart, hit spans of high scores too unevenly: a row whose seed came
+//      out above its k-th key is streamed again);
 //   2. streaming filter: each wave takes 1 KB chunks of its own, TK_RING of
 //      them in flight in registers, and appends what it accepts with one LDS
 //      atomic per chunk that has any.  The waves meet only when the row is
@@ -15,7 +17,7 @@
 //      the buffer is then cut to exactly the k best, the threshold rises to
 //      the k-th best (key, id), and the stopped waves go on, so no member of
 //      the answer is lost.  If the seed was above the k-th key (fewer than k
-//      passed), the row is streamed again with no threshold;
+//      passed), the row is streamed again with a looser one, then with none;
 //   3. exact selection from registers: the keys' range is narrowed to one of
 //      2048 equal bins, and again, until the bin holding the k-th key has few
 //      enough entries to be ranked pairwise, or is a single key, whose ties
@@ -30,8 +32,8 @@
 // 8-bit digits from the top took four (the first ones all but one bin wide,
 // their atomics serialised), register scans replace shuffles, and waves that
 // stream on their own need no barrier per stage.  Measured (k = 2048 unless
-// stated): 4096 rows of 135K 500 -> 413 us (5.4 TB/s), 64 rows of 32K-158K 51
-// -> 30, 512 shards of 16K (k = 256) 21 -> 13, one row of 13K 27 -> 15, 2048
+// stated): 4096 rows of 135K 500 -> 400 us (5.5 TB/s), 64 rows of 32K-158K 55
+// -> 24, 512 shards of 16K (k = 256) 21 -> 13, one row of 13K 27 -> 15, 2048
 // rows of 8.2K (k = 512) 90 -> 50.
 #include "janus_device.hpp"
 #include "janus_host.hpp"
@@ -44,7 +46,7 @@ namespace janus {
 constexpr int TK_RING = 8;                // 1 KB chunks in flight per wave
 constexpr int TK_MAX_K = 6144;            // with CAP = 8192: >= 2048 free slots after a cut
 constexpr int TK_SMALL_K = 2048;          // with CAP = 4096
-constexpr int TK_SAMPLE_LINES = 128;      // ~1/32 of a 128K row, in 32-element lines
+constexpr int TK_SAMPLE_GROUPS = 512;     // ~1/32 of a 128K row, in 8-element groups
 constexpr int TK_BINS = 2048;
 constexpr int TK_FEW = 64;                // entries of a bin that are ranked pairwise
 
@@ -360,10 +362,10 @@ JANUS_DEV bool append4(SM &sm, v4f x, uint32_t pend, int id0, float tf, int32_t 
 }
 
 // One pass over [0, n) of the row, filtering against the running threshold;
-// with `seed`, the threshold is first set from a sample of the row.  Ends with
-// a barrier.
+// with seed > 0 the threshold is first set from a sample of the row, so that
+// about seed * k elements pass.  Ends with a barrier.
 template <int TPB, int CAP>
-JANUS_DEV void stream_row(TopkShared<TPB, CAP> &sm, const float *__restrict__ row, int n, int k, bool seed)
+JANUS_DEV void stream_row(TopkShared<TPB, CAP> &sm, const float *__restrict__ row, int n, int k, float seed)
 {
     constexpr int NW = TPB / kWave;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -380,15 +382,15 @@ JANUS_DEV void stream_row(TopkShared<TPB, CAP> &sm, const float *__restrict__ ro
 
     // the sample goes out first, then the head and tail elements and the
     // wave's first chunks; the sample is ranked under their latency
-    constexpr int SPT = TK_SAMPLE_LINES * 8 / TPB;  // float4s of the sample per thread
-    const int nlines = nbody4 >> 3;
-    const int stride = max(1, nlines / TK_SAMPLE_LINES);
-    const int m4 = seed ? min(TK_SAMPLE_LINES, nlines) * 8 : 0;
+    constexpr int SPT = TK_SAMPLE_GROUPS * 2 / TPB;  // float4s of the sample per thread
+    const int ngroups = nbody4 >> 1;
+    const int stride = max(1, ngroups / TK_SAMPLE_GROUPS);
+    const int m4 = seed > 0.f ? min(TK_SAMPLE_GROUPS, ngroups) * 2 : 0;
     v4f smp[SPT];
 #pragma unroll
     for (int j = 0; j < SPT; ++j) {
         const int e = (int)threadIdx.x + j * TPB;
-        smp[j] = load4(e < m4 ? (e >> 3) * stride * 8 + (e & 7) : nbody4);
+        smp[j] = load4(e < m4 ? (e >> 1) * stride * 2 + (e & 1) : nbody4);
     }
     // lanes 0..2 of the first wave take the head, 4..6 the tail
     const int hti = lane < 4 ? lane : tail0 + lane - 4;
@@ -399,7 +401,7 @@ JANUS_DEV void stream_row(TopkShared<TPB, CAP> &sm, const float *__restrict__ ro
     for (int u = 0; u < TK_RING; ++u)
         x[u] = load4((wave + u * NW) * kWave + lane);
 
-    if (seed) {
+    if (seed > 0.f) {
         uint32_t key[4 * SPT], on = 0, lo = 0xffffffffu, hi = 0u;
 #pragma unroll
         for (int j = 0; j < SPT; ++j)
@@ -414,9 +416,9 @@ JANUS_DEV void stream_row(TopkShared<TPB, CAP> &sm, const float *__restrict__ ro
                 }
             }
         block_extremes(sm, lo, hi);
-        // rank ~ 1.3 * k * (sample / n) + 8; the bin's lower end suffices once
+        // rank ~ seed * k * (sample / n) + 8; the bin's lower end suffices once
         // the bin holds few of that rank's entries
-        int r = min(4 * m4, (int)(1.3f * (float)k * (float)(4 * m4) / (float)n) + 8);
+        int r = min(4 * m4, (int)(seed * (float)k * (float)(4 * m4) / (float)n) + 8);
         narrow<TPB>(sm, key, on, lo, hi, r, max(4, r >> 3));
         if (threadIdx.x == 0)
             set_threshold(sm, lo, 0x7fffffff);  // accept key >= seed
@@ -455,6 +457,24 @@ JANUS_DEV void stream_row(TopkShared<TPB, CAP> &sm, const float *__restrict__ ro
         if (sm.count <= CAP)
             break;
         compact(sm, k);
+    }
+}
+
+// After a seed above the k-th key: the row again with a looser seed, then with
+// none.  Begins with a barrier.
+template <int TPB, int CAP>
+__device__ __noinline__ void stream_again(TopkShared<TPB, CAP> &sm, const float *row, int n, int k)
+{
+    for (float seed = n > CAP ? 3.f : 0.f;; seed = 0.f) {
+        lds_sync();
+        if (threadIdx.x == 0) {
+            sm.count = 0;
+            set_threshold(sm, 0u, 0x7fffffff);
+        }
+        lds_sync();
+        stream_row<TPB, CAP>(sm, row, n, k, seed);
+        if (sm.count >= k || seed == 0.f)
+            break;
     }
 }
 
@@ -499,17 +519,10 @@ __global__ __launch_bounds__(TPB, CAP <= 4096 ? 4 : 2) void topk_rows(
     }
     lds_sync();
 
-    // 1., 2. one streaming pass (two if the seed was above the k-th key)
-    stream_row<TPB, CAP>(sm, row, n, k, n > CAP);
-    if (sm.count < k) {
-        lds_sync();
-        if (threadIdx.x == 0) {
-            sm.count = 0;
-            set_threshold(sm, 0u, 0x7fffffff);
-        }
-        lds_sync();
-        stream_row<TPB, CAP>(sm, row, n, k, false);
-    }
+    // 1., 2. one streaming pass (more if the seed was above the k-th key)
+    stream_row<TPB, CAP>(sm, row, n, k, n > CAP ? 1.3f : 0.f);
+    if (sm.count < k)
+        stream_again<TPB, CAP>(sm, row, n, k);
     // 3. the k best of the buffered candidates
     const int cnt = sm.count;
     constexpr int NI = CAP / TPB;

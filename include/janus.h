@@ -240,6 +240,7 @@ int janus_page_demand(const janus_batch *b, const int32_t *topk_idx, int k,
  *   miss               device [ceil(num_phys_pages/32)] uint32: A & ~P
  *   miss_runs          device [2*num_phys_pages] int32 (start, length) pairs
  *   counts             device [5] int32: {|A|, |P|, |A&P|, |A&~P|, #miss runs}
+ * miss may be the array that actual or predicted is in.
  * Requires num_phys_pages <= 2^19 (else JANUS_ERR_UNSUPPORTED) and
  * max_run >= 1.
  */

@@ -339,7 +339,8 @@ JANUS_DEV uint32_t masked_word(const uint32_t *bm, int w, int nbits)
 
 __global__ __launch_bounds__(RUN_THREADS) void page_list_runs(const uint32_t *__restrict__ bitmap, int nbits,
                                                               int max_run, int32_t *__restrict__ list,
-                                                              int32_t *__restrict__ runs, int32_t *__restrict__ counts)
+                                                              int32_t *__restrict__ runs, int32_t *n_pages,
+                                                              int32_t *n_runs)
 {
     __shared__ RunShared sh;
     extern __shared__ uint32_t sw[];  // the bitmap's words
@@ -347,7 +348,7 @@ __global__ __launch_bounds__(RUN_THREADS) void page_list_runs(const uint32_t *__
     for (int w = threadIdx.x; w < nwords; w += RUN_THREADS)
         sw[w] = masked_word(bitmap, w, nbits);
     lds_sync();
-    emit_list_runs(sh, sw, nbits, max_run, list, runs, counts, counts + 1);
+    emit_list_runs(sh, sw, nbits, max_run, list, runs, n_pages, n_runs);
 }
 
 // All of page demand in one block
@@ -370,9 +371,11 @@ __global__ __launch_bounds__(RUN_THREADS) void page_demand_small(UnionArgs u, in
     emit_list_runs(sh, sw, nbits, max_run, list, runs, counts, counts + 1);
 }
 
-__global__ __launch_bounds__(RUN_THREADS) void predict_diff_kernel(
-    const uint32_t *__restrict__ actual, const uint32_t *__restrict__ predicted, int nbits, int max_run,
-    uint32_t *__restrict__ miss, int32_t *__restrict__ miss_runs, int32_t *__restrict__ counts)
+// A block reads both bitmaps whole before it writes anything, so that one
+// block alone may write over them (in place: see the launch).
+__global__ __launch_bounds__(RUN_THREADS) void predict_diff_kernel(const uint32_t *actual, const uint32_t *predicted,
+                                                                   int nbits, int max_run, uint32_t *miss,
+                                                                   int32_t *miss_runs, int32_t *counts)
 {
     __shared__ RunShared sh;
     extern __shared__ uint32_t sw[];  // the miss set's words
@@ -384,8 +387,6 @@ __global__ __launch_bounds__(RUN_THREADS) void predict_diff_kernel(
         cp += __popc(p);
         cap += __popc(a & p);
         sw[w] = a & ~p;
-        if (blockIdx.x == 0)
-            miss[w] = a & ~p;
     }
     if (blockIdx.x == 0) {
         int na, np, nap, unused, one = 0;
@@ -399,6 +400,9 @@ __global__ __launch_bounds__(RUN_THREADS) void predict_diff_kernel(
         }
     }
     lds_sync();  // the staged words are read from here on
+    if (blockIdx.x == 0)
+        for (int w = threadIdx.x; w < nwords; w += RUN_THREADS)
+            miss[w] = sw[w];
     emit_list_runs(sh, sw, nbits, max_run, nullptr, miss_runs, nullptr, counts + 4);
 }
 
@@ -442,7 +446,7 @@ extern "C" int janus_page_demand(const janus_batch *bt, const int32_t *topk_idx,
         hipLaunchKernelGGL(page_union, dim3(std::min<int>(PD_MAX_BLOCKS, bt->total_q)), dim3(PD_THREADS), lds, st, u,
                            (int)bt->total_q, nwords, bitmap);
     hipLaunchKernelGGL(page_list_runs, dim3(run_blocks(nwords)), dim3(RUN_THREADS), lds, st, bitmap, num_phys_pages,
-                       max_run, page_list, runs, counts);
+                       max_run, page_list, runs, counts, counts + 1);
     return launch_status();
 }
 
@@ -453,9 +457,22 @@ extern "C" int janus_predict_diff(const uint32_t *actual, const uint32_t *predic
         return JANUS_ERR_INVALID_ARG;
     if (num_phys_pages > PD_MAX_PAGES)
         return JANUS_ERR_UNSUPPORTED;
-    const int nwords = (num_phys_pages + 31) >> 5;
-    hipLaunchKernelGGL(predict_diff_kernel, dim3(run_blocks(nwords)), dim3(RUN_THREADS),
-                       std::max(nwords, 1) * sizeof(uint32_t), as_stream(stream), actual, predicted, num_phys_pages,
-                       max_run, miss, miss_runs, counts);
+    const int nwords = (num_phys_pages + 31) >> 5, nblk = run_blocks(nwords);
+    const size_t words = (size_t)nwords * sizeof(uint32_t), lds = std::max<size_t>(words, sizeof(uint32_t));
+    auto over = [&](const void *out, size_t n, const void *in) {
+        const uintptr_t a = reinterpret_cast<uintptr_t>(out), b = reinterpret_cast<uintptr_t>(in);
+        return a < b + words && b < a + n;
+    };
+    auto over_inputs = [&](const void *out, size_t n) { return over(out, n, actual) || over(out, n, predicted); };
+    // an output over an input: the other blocks would still read what the
+    // first one writes, so one block writes the miss set and the counts, and
+    // a launch after it the runs of all slices
+    const bool alone = nblk > 1 && (over_inputs(miss, words) || over_inputs(counts, 5 * sizeof(int32_t)) ||
+                                    over_inputs(miss_runs, 2 * sizeof(int32_t) * (size_t)num_phys_pages));
+    hipLaunchKernelGGL(predict_diff_kernel, dim3(alone ? 1 : nblk), dim3(RUN_THREADS), lds, as_stream(stream), actual,
+                       predicted, num_phys_pages, max_run, miss, miss_runs, counts);
+    if (alone)
+        hipLaunchKernelGGL(page_list_runs, dim3(nblk), dim3(RUN_THREADS), lds, as_stream(stream), miss, num_phys_pages,
+                           max_run, (int32_t *)nullptr, miss_runs, (int32_t *)nullptr, counts + 4);
     return launch_status();
 }

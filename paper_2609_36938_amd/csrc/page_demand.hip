@@ -366,8 +366,11 @@ __global__ __launch_bounds__(RUN_THREADS) void page_demand_small(UnionArgs u, in
     lds_sync();
     union_rows<RUN_THREADS>(u, 0, total_q, sw);
     lds_sync();
-    for (int w = threadIdx.x; w < nwords; w += RUN_THREADS)
+    for (int w = threadIdx.x; w < nwords; w += RUN_THREADS) {
         bitmap[w] = sw[w];
+        sw[w] = masked_word(sw, w, nbits);  // (no page past the pool is listed, whatever the table holds)
+    }
+    lds_sync();
     emit_list_runs(sh, sw, nbits, max_run, list, runs, counts, counts + 1);
 }
 

@@ -13,7 +13,7 @@
 // emits a slice of RUN_THREADS words, one word per thread: what lies before
 // the slice (pages, run starts, the last unset page) it counts itself, so that
 // the slices need nothing from each other.
-// Few ids: one block does all of it, in one launch instead of three.
+// Few rows: one block does all of it, in one launch instead of three.
 //
 // What bounds all of these is latency: chains of loads and barriers, and the
 // launches.  Measured: the union of 4096 rows of 2048 ids 28 -> 10 us, of 64
@@ -21,6 +21,7 @@
 // two rows in one launch 7.6 us instead of 1 + 7 + 12 in three.
 #include "janus_device.hpp"
 #include "janus_host.hpp"
+#include "launch_rules.hpp"
 
 #include <algorithm>
 
@@ -28,9 +29,6 @@ namespace janus {
 
 constexpr int PD_THREADS = 512;
 constexpr int PD_MAX_BLOCKS = 1024;
-constexpr int PD_ROWS = 4;          // rows in flight per block
-constexpr int PD_SMALL_IDS = 16384; // up to this many ids one block does everything
-constexpr int RUN_THREADS = 1024;
 constexpr int RUN_WAVES = RUN_THREADS / kWave;
 constexpr int PD_MAX_PAGES = 1 << 19;  // 64 KB LDS bitmap
 
@@ -241,15 +239,18 @@ JANUS_DEV int count_starts(int w, uint32_t v, int last_zero, int max_run, FirstZ
     return n;
 }
 
-// Walks the pages of the bitmap sw in LDS (nbits bits, zeros past them; whole
-// 32-bit words): writes, for this block's slice of RUN_THREADS words, one per
-// thread, the ascending page list (if list != NULL) and the packed runs, and in
+// Walks the pages of the bitmap sw in LDS (nbits bits, zeros past them unless
+// MASK: then those bits are ignored; whole 32-bit words): writes, for this
+// block's slice of RUN_THREADS words, one per thread, the ascending page list (if list != NULL) and the packed runs, and in
 // the first block the two counts.
+template <bool MASK>
 JANUS_DEV void emit_list_runs(RunShared &sh, const uint32_t *sw, int nbits, int max_run, int32_t *list, int32_t *runs,
                               int32_t *n_pages_out, int32_t *n_runs_out)
 {
     const int nwords = (nbits + 31) >> 5, tid = threadIdx.x;
     const int wpt = max(1, (nwords + RUN_THREADS - 1) / RUN_THREADS);  // words of a thread's range
+    const uint32_t last_mask = nbits & 31 ? (1u << (nbits & 31)) - 1u : ~0u;
+    auto word = [&](int w) { return MASK && w == nwords - 1 ? sw[w] & last_mask : sw[w]; };
     auto last_unset = [&](int w, uint32_t v) { return (w << 5) + 31 - __clz((int)~v); };  // v not all ones
     // over ranges of wpt words: the first unset page from each range on
     // (ranges taken from the end), the last one before each
@@ -258,12 +259,12 @@ JANUS_DEV void emit_list_runs(RunShared &sh, const uint32_t *sw, int nbits, int 
         const int t = RUN_THREADS - 1 - tid, e0 = min(nwords, t * wpt), e1 = min(nwords, e0 + wpt);
         int fz = nbits, lz = -1, tf, tl;
         for (int w = e1 - 1; w >= e0; --w)
-            if (sw[w] != 0xffffffffu)
-                fz = min(nbits, (w << 5) + __ffs(~sw[w]) - 1);
+            if (word(w) != 0xffffffffu)
+                fz = min(nbits, (w << 5) + __ffs(~word(w)) - 1);
         const int a0 = min(nwords, tid * wpt), a1 = min(nwords, a0 + wpt);
         for (int w = a0; w < a1; ++w)
-            if (sw[w] != 0xffffffffu)
-                lz = last_unset(w, sw[w]);
+            if (word(w) != 0xffffffffu)
+                lz = last_unset(w, word(w));
         run_scan2(sh.a, sh.b, lz, -1, op_max, fz, nbits, op_min, before, tl, tf);
         sh.fz[t] = fz;
     }
@@ -272,20 +273,20 @@ JANUS_DEV void emit_list_runs(RunShared &sh, const uint32_t *sw, int nbits, int 
         for (int x = w + 1; x < nwords; ++x) {
             if (wpt == 1 || x % wpt == 0)  // a range's first word
                 return sh.fz[wpt == 1 ? x : x / wpt];
-            if (sw[x] != 0xffffffffu)
-                return min(nbits, (x << 5) + __ffs(~sw[x]) - 1);
+            if (word(x) != 0xffffffffu)
+                return min(nbits, (x << 5) + __ffs(~word(x)) - 1);
         }
         return nbits;
     };
     // one slice, and what lies before it: nothing, or counted here
     const int s0 = blockIdx.x * RUN_THREADS, w = s0 + tid;
-    const uint32_t v = w < nwords ? sw[w] : 0u;
+    const uint32_t v = w < nwords ? word(w) : 0u;
     int pages_before = 0, starts_before = 0, lb = before, unused;
     if (wpt > 1) {
         int pages = 0, starts = 0, L = before, zl = -1, zero_before, one = 0;
         const int a0 = min(nwords, tid * wpt), a1 = min(nwords, a0 + wpt);
         for (int x = a0; x < a1; ++x) {
-            const uint32_t y = sw[x];
+            const uint32_t y = word(x);
             if (s0 == 0 || x < s0) {  // (the first block counts everything, for the totals)
                 pages += __popc(y);
                 starts += count_starts(x, y, L, max_run, first_zero);
@@ -348,7 +349,7 @@ __global__ __launch_bounds__(RUN_THREADS) void page_list_runs(const uint32_t *__
     for (int w = threadIdx.x; w < nwords; w += RUN_THREADS)
         sw[w] = masked_word(bitmap, w, nbits);
     lds_sync();
-    emit_list_runs(sh, sw, nbits, max_run, list, runs, n_pages, n_runs);
+    emit_list_runs<false>(sh, sw, nbits, max_run, list, runs, n_pages, n_runs);
 }
 
 // All of page demand in one block
@@ -366,12 +367,9 @@ __global__ __launch_bounds__(RUN_THREADS) void page_demand_small(UnionArgs u, in
     lds_sync();
     union_rows<RUN_THREADS>(u, 0, total_q, sw);
     lds_sync();
-    for (int w = threadIdx.x; w < nwords; w += RUN_THREADS) {
+    for (int w = threadIdx.x; w < nwords; w += RUN_THREADS)
         bitmap[w] = sw[w];
-        sw[w] = masked_word(sw, w, nbits);  // (no page past the pool is listed, whatever the table holds)
-    }
-    lds_sync();
-    emit_list_runs(sh, sw, nbits, max_run, list, runs, counts, counts + 1);
+    emit_list_runs<true>(sh, sw, nbits, max_run, list, runs, counts, counts + 1);
 }
 
 // A block reads both bitmaps whole before it writes anything, so that one
@@ -406,7 +404,7 @@ __global__ __launch_bounds__(RUN_THREADS) void predict_diff_kernel(const uint32_
     if (blockIdx.x == 0)
         for (int w = threadIdx.x; w < nwords; w += RUN_THREADS)
             miss[w] = sw[w];
-    emit_list_runs(sh, sw, nbits, max_run, nullptr, miss_runs, nullptr, counts + 4);
+    emit_list_runs<false>(sh, sw, nbits, max_run, nullptr, miss_runs, nullptr, counts + 4);
 }
 
 } // namespace janus
@@ -436,9 +434,7 @@ extern "C" int janus_page_demand(const janus_batch *bt, const int32_t *topk_idx,
     const int vec = k % 4 == 0 && (reinterpret_cast<uintptr_t>(topk_idx) & 15) == 0;
     const UnionArgs u = {bt->q_start, bt->hist_len, bt->num_seqs, bt->entry_shift, topk_idx, k, vec, page_table,
                          pt_ld, __builtin_ctz((unsigned)page_size), limit};
-    // one block looks up an id about as fast as the launches it saves take
-    // for PD_SMALL_IDS of them
-    if (bt->total_q > 0 && nwords > 0 && (int64_t)bt->total_q * k <= PD_SMALL_IDS && nwords <= RUN_THREADS) {
+    if (pd_one_block(bt->total_q, k, nwords)) {
         hipLaunchKernelGGL(page_demand_small, dim3(1), dim3(RUN_THREADS), lds, st, u, (int)bt->total_q,
                            num_phys_pages, max_run, bitmap, page_list, runs, counts);
         return launch_status();

@@ -1,0 +1,34 @@
+"""The rules that pick kernels and launch shapes, compiled for the host and
+checked on their own."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2609_36938_amd", "csrc")
+WRAP = r"""
+#include "launch_rules.hpp"
+extern "C" {
+int pd_one_block(long q, long k, int nwords) { return janus::pd_one_block(q, k, nwords); }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    (d / "r.cpp").write_text(WRAP)
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-Wall", "-shared", "-fPIC", "-I", CSRC, str(d / "r.cpp"), "-o",
+                           str(d / "r.so")])
+    return ctypes.CDLL(str(d / "r.so"))
+
+
+def test_page_demand_one_block(rules):
+    one = lambda q, k, nw=40: bool(rules.pd_one_block(ctypes.c_long(q), ctypes.c_long(k), nw))  # noqa: E731
+    for q, k in [(1, 1), (2, 2048), (8, 2048), (8, 1), (4, 8192)]:
+        assert one(q, k), (q, k)
+    # rows are walked one step after another, whatever their ids: many rows take blocks of their own
+    for q, k in [(256, 64), (16384, 1), (4096, 4), (64, 256), (128, 128), (9, 1), (8, 8192), (0, 5)]:
+        assert not one(q, k), (q, k)
+    assert one(2, 64, 1024) and not one(2, 64, 1025) and not one(2, 64, 0)

@@ -401,9 +401,8 @@ __global__ __launch_bounds__(RUN_THREADS) void predict_diff_kernel(const uint32_
         }
     }
     lds_sync();  // the staged words are read from here on
-    if (blockIdx.x == 0)
-        for (int w = threadIdx.x; w < nwords; w += RUN_THREADS)
-            miss[w] = sw[w];
+    for (int w = blockIdx.x * RUN_THREADS + threadIdx.x; w < nwords; w += gridDim.x * RUN_THREADS)
+        miss[w] = sw[w];
     emit_list_runs<false>(sh, sw, nbits, max_run, nullptr, miss_runs, nullptr, counts + 4);
 }
 

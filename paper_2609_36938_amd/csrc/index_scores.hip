@@ -30,6 +30,7 @@
 // with the one a VALU write of an MFMA source needs.
 #include "janus_device.hpp"
 #include "janus_host.hpp"
+#include "launch_rules.hpp"
 
 #include <algorithm>
 #include <cmath>
@@ -1104,26 +1105,22 @@ constexpr int ROWS_CHUNK_MIN = 256;
 constexpr int ROWS_CHUNK_GRID = 1024;  // the chunk that a launch's grid is checked for; shorter ones only where they fit
 constexpr int ROWS_BLOCK_KEYS = 128;   // what a block costs besides its keys, in keys
 
-// Block -> (session, first key): the session's lane holds the block's number
-// in the wave's prefix sums of chunk counts (chunk = 2^shift), 64 sessions a
-// step.  Scalar results; b = -1 past the last block.
+// Block -> (session, first key), chunks of 2^shift keys, blocks numbered by
+// rows_first.  The wave looks for the session 64 ways a step: one step up to 64
+// sessions, two up to 4096 (a scan of the chunk counts took a step per 64
+// sessions: 4096 sessions of 1000 keys 288 us, now 145).  Scalar results.
 JANUS_DEV void rows_block(const int32_t *ctx_start, int num_seqs, int shift, int block, int &b, int &c0)
 {
-    int left = block, s0 = 0;  // blocks of this step's sessions and later ones
-    for (;;) {
-        const int s = s0 + (int)(threadIdx.x & 63);
-        const int n = s < num_seqs ? (ctx_start[s + 1] - ctx_start[s] + (1 << shift) - 1) >> shift : 0;
-        const int incl = wave_sum_scan(n);
-        const uint64_t past = __ballot(incl > left);
-        const int l = past ? __builtin_ctzll(past) : 63;
-        const int upto = __builtin_amdgcn_readlane(incl, l);
-        b = past ? s0 + l : -1;
-        c0 = (left - (upto - __builtin_amdgcn_readlane(n, l))) << shift;
-        left -= upto;
-        s0 += kWave;
-        if (past || s0 >= num_seqs)
-            break;
+    const int lane = threadIdx.x & 63;
+    b = 0;
+    for (int n = num_seqs; n > 1;) {  // the session is one of b .. b + n - 1
+        const int step = (n + kWave - 1) / kWave, s = b + min(lane * step, n - 1);
+        const int first = rows_first(ctx_start[s], s, shift);  // (by every lane: a load behind a branch cost registers)
+        const int at = (__popcll(__ballot(lane * step < n && first <= block)) - 1) * step;
+        b += at;
+        n = min(step, n - at);
     }
+    c0 = (block - rows_first(ctx_start[b], b, shift)) << shift;
 }
 
 template <int NQ, bool FP4>
@@ -1136,13 +1133,10 @@ __global__ __launch_bounds__(256, 2) void index_scores_rows(
 {
     // one token per session: blocks numbered session by session, chunk by
     // chunk (a grid of the longest session's chunks for each was nearly half
-    // empty blocks); more tokens: that grid, chunk fastest (behind the search
-    // the compiler needs more registers than these instances have)
+    // empty blocks); more tokens: that grid, chunk fastest
     int b, c0;
     if constexpr (NQ == 1) {
         rows_block(ctx_start, num_seqs, 31 - __builtin_clz(chunk), (int)blockIdx.x, b, c0);
-        if (b < 0)
-            return;
     } else {
         b = blockIdx.x / nchunks;
         c0 = (blockIdx.x - b * nchunks) * chunk;

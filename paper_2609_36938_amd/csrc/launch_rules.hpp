@@ -29,4 +29,11 @@ constexpr bool pd_one_block(int64_t total_q, int64_t k, int nwords)
     return total_q > 0 && nwords > 0 && nwords <= RUN_THREADS && pd_steps(total_q, k) <= PD_SMALL_STEPS;
 }
 
+// ---- decode indexer: blocks of a batch ----------------------------------------
+
+// First block of session s, whose keys start at ctx_start, in chunks of 2^shift
+// keys: each session has as many blocks as chunks, or one more, and no block
+// needs the sessions before its own.
+constexpr int rows_first(int ctx_start, int s, int shift) { return (ctx_start >> shift) + s; }
+
 } // namespace janus

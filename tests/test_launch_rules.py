@@ -4,6 +4,7 @@ import ctypes
 import os
 import subprocess
 
+import numpy as np
 import pytest
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2609_36938_amd", "csrc")
@@ -11,6 +12,7 @@ WRAP = r"""
 #include "launch_rules.hpp"
 extern "C" {
 int pd_one_block(long q, long k, int nwords) { return janus::pd_one_block(q, k, nwords); }
+int rows_first(int ctx_start, int s, int shift) { return janus::rows_first(ctx_start, s, shift); }
 }
 """
 
@@ -32,3 +34,16 @@ def test_page_demand_one_block(rules):
     for q, k in [(256, 64), (16384, 1), (4096, 4), (64, 256), (128, 128), (9, 1), (8, 8192), (0, 5)]:
         assert not one(q, k), (q, k)
     assert one(2, 64, 1024) and not one(2, 64, 1025) and not one(2, 64, 0)
+
+
+@pytest.mark.parametrize("shift", [8, 10, 11])
+def test_decode_blocks_cover_every_chunk(rules, shift):
+    rng = np.random.default_rng(shift)
+    for n in (1, 2, 63, 64, 65, 1000):
+        ctx = np.where(rng.random(n) < 0.2, 0, np.exp(rng.uniform(0, 12, n)).astype(np.int64))
+        ctx[rng.integers(n)] = 7 << shift
+        start = np.concatenate([[0], np.cumsum(ctx)])
+        first = [rules.rows_first(int(start[s]), s, shift) for s in range(n)] + [(int(start[-1]) >> shift) + n]
+        for s in range(n):
+            chunks = -(-int(ctx[s]) >> shift)
+            assert chunks <= first[s + 1] - first[s] <= chunks + 1

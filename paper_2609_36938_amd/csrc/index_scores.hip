@@ -33,7 +33,6 @@
 #include "launch_rules.hpp"
 
 #include <algorithm>
-#include <cmath>
 
 namespace janus {
 
@@ -1085,7 +1084,7 @@ __global__ __launch_bounds__(256, 4) void index_scores_general(
 namespace janus {
 
 // Row-tile kernel: a block takes up to NQ tokens of one session and one
-// chunk of 256 to 4096 keys (chosen per launch).  It serves
+// chunk of 256 to 2048 keys (rows_plan).  It serves
 // decode-shaped batches (every session appends at most NQ tokens, as in the
 // decode phase: the scores are a GEMV over each session's keys, bound by
 // reading the keys once), with fp8 or MXFP4 keys.  The four waves take the
@@ -1100,10 +1099,6 @@ namespace janus {
 // group: one 256-byte store per token and group; groups wholly past every
 // token's causal limit skip the MFMAs (their stores write -inf).
 constexpr int ROWS_NQ = 4;
-constexpr int ROWS_CHUNK_MAX = 4096;   // keys per block: 4096, 2048, .. 256
-constexpr int ROWS_CHUNK_MIN = 256;
-constexpr int ROWS_CHUNK_GRID = 1024;  // the chunk that a launch's grid is checked for; shorter ones only where they fit
-constexpr int ROWS_BLOCK_KEYS = 128;   // what a block costs besides its keys, in keys
 
 // Block -> (session, first key), chunks of 2^shift keys, blocks numbered by
 // rows_first.  The wave looks for the session 64 ways a step: one step up to 64
@@ -1126,20 +1121,18 @@ JANUS_DEV void rows_block(const int32_t *ctx_start, int num_seqs, int shift, int
 template <int NQ, bool FP4>
 __global__ __launch_bounds__(256, 2) void index_scores_rows(
     const int32_t *__restrict__ q_start, const int32_t *__restrict__ ctx_start,
-    const int32_t *__restrict__ hist_len, const int64_t *__restrict__ score_start, int num_seqs, int es, int nchunks,
+    const int32_t *__restrict__ hist_len, const int64_t *__restrict__ score_start, int num_seqs, int es, int per_seq,
     int chunk, const uint8_t *__restrict__ q, const float *__restrict__ q_scale, const uint8_t *__restrict__ kI,
     const uint8_t *__restrict__ k_bscale, const float *__restrict__ k_scale, const float *__restrict__ w,
     float *__restrict__ scores)
 {
-    // one token per session: blocks numbered session by session, chunk by
-    // chunk (a grid of the longest session's chunks for each was nearly half
-    // empty blocks); more tokens: that grid, chunk fastest
+    // per_seq blocks for each session, chunk fastest, or (0) numbered by rows_first
     int b, c0;
-    if constexpr (NQ == 1) {
-        rows_block(ctx_start, num_seqs, 31 - __builtin_clz(chunk), (int)blockIdx.x, b, c0);
+    if (per_seq > 0) {
+        b = blockIdx.x / per_seq;
+        c0 = (blockIdx.x - b * per_seq) * chunk;
     } else {
-        b = blockIdx.x / nchunks;
-        c0 = (blockIdx.x - b * nchunks) * chunk;
+        rows_block(ctx_start, num_seqs, 31 - __builtin_clz(chunk), (int)blockIdx.x, b, c0);
     }
     constexpr int t0 = 0;
     const int qs = q_start[b], N = q_start[b + 1] - qs;
@@ -1346,57 +1339,22 @@ static bool rows_grid_ok(const janus_batch *bt)
     const int nq = rows_nq(bt);
     const int64_t tiles =
         bt->max_q <= nq ? bt->num_seqs : ceil_div(bt->total_q, nq) + (int64_t)bt->num_seqs;
-    return tiles * ceil_div(bt->max_ctx, ROWS_CHUNK_GRID) <= INT32_MAX;
+    return tiles * ceil_div(bt->max_ctx, 1024) <= INT32_MAX;
 }
-// Blocks of a launch.  One token per session: at most this many chunks (every
-// session's last one may be partial); else the longest session's for each.
-static int64_t rows_blocks(const janus_batch *bt, int chunk)
-{
-    return rows_nq(bt) == 1 ? bt->total_ctx / chunk + bt->num_seqs
-                            : (int64_t)bt->num_seqs * ceil_div(bt->max_ctx, chunk);
-}
-
-// Keys per block, 4096 down to 256 (one 64-key group per wave).  The blocks
-// run in rounds of the GPU's resident block slots, each as long as a chunk and
-// what a block pays besides (loading its tokens' queries, about as long as
-// ROWS_BLOCK_KEYS more keys): take the chunk with the shortest total.  A full
-// batch (5M keys in 64 sessions) gets 1024 keys, a small one the shortest:
-// two sessions of 28K keys in all took 21 us as 8 blocks of 4096 keys, and
-// 6 as 109 of 256.  A session of C keys makes about C/chunk + 1/2 blocks.
-template <typename Kern>
-static int rows_chunk(const janus_batch *bt, Kern kern)
-{
-    int dev = 0, cus = 0, per = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, 256, 0) != hipSuccess || cus < 1 || per < 1)
-        return ROWS_CHUNK_MAX;
-    const double slots = (double)per * cus;
-    int best = ROWS_CHUNK_MAX;
-    double best_cost = 0.0;
-    for (int c = ROWS_CHUNK_MAX; c >= ROWS_CHUNK_MIN; c /= 2) {
-        if (c < ROWS_CHUNK_GRID && rows_blocks(bt, c) > (1 << 24) - 1)
-            break;  // a launch takes fewer than 2^32 threads
-        const double blocks = (double)bt->total_ctx / c + 0.5 * bt->num_seqs;
-        const double cost = std::ceil(blocks / slots) * (c + ROWS_BLOCK_KEYS);
-        if (c == ROWS_CHUNK_MAX || cost < best_cost) {
-            best_cost = cost;
-            best = c;
-        }
-    }
-    return best;
-}
-
 template <bool FP4>
 static void launch_rows(const janus_batch *bt, const void *q, const float *q_scale, const void *kI,
                         const uint8_t *k_bscale, const float *k_scale, const float *w, float *scores, hipStream_t st)
 {
     const int nq = rows_nq(bt);
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+        cus = 256;
+    const RowsPlan p = rows_plan(bt->num_seqs, bt->max_ctx, bt->total_ctx, cus, FP4);
     auto go = [&](auto kern) {
-        const int chunk = rows_chunk(bt, kern);
-        hipLaunchKernelGGL(kern, dim3((unsigned)rows_blocks(bt, chunk)), dim3(256), 0, st, bt->q_start, bt->ctx_start,
-                           bt->hist_len, bt->score_start, bt->num_seqs, bt->entry_shift,
-                           ceil_div(bt->max_ctx, chunk), chunk, (const uint8_t *)q, q_scale, (const uint8_t *)kI, k_bscale, k_scale, w, scores);
+        hipLaunchKernelGGL(kern, dim3((unsigned)p.blocks), dim3(256), 0, st, bt->q_start, bt->ctx_start, bt->hist_len,
+                           bt->score_start, bt->num_seqs, bt->entry_shift, p.per_seq, p.chunk, (const uint8_t *)q,
+                           q_scale, (const uint8_t *)kI, k_bscale, k_scale, w, scores);
     };
     if (nq == 1)
         go(index_scores_rows<1, FP4>);
@@ -1429,7 +1387,7 @@ extern "C" int janus_index_scores(const janus_batch *bt, const void *q, janus_dt
     // with 32-bit buffer offsets: contexts up to 2^24 tokens
     if (q_dt == JANUS_FP8_E4M3 && d == 128 && H == 64 && bt->max_ctx <= (1 << 24) && bt->max_q <= ROWS_NQ &&
         rows_grid_ok(bt)) {
-        // decode-shaped: one block per (session, 4096-key chunk)
+        // decode-shaped: the row-tile kernel
         launch_rows<false>(bt, q, q_scale, kI, nullptr, k_scale, w, scores, st);
         return launch_status();
     }

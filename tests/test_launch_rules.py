@@ -12,6 +12,11 @@ WRAP = r"""
 #include "launch_rules.hpp"
 extern "C" {
 int pd_one_block(long q, long k, int nwords) { return janus::pd_one_block(q, k, nwords); }
+void rows_plan(int n, int max_ctx, long total, int cus, int fp4, long *out)
+{
+    const janus::RowsPlan p = janus::rows_plan(n, max_ctx, total, cus, fp4);
+    out[0] = p.chunk, out[1] = p.per_seq, out[2] = p.blocks;
+}
 int rows_first(int ctx_start, int s, int shift) { return janus::rows_first(ctx_start, s, shift); }
 }
 """
@@ -47,3 +52,30 @@ def test_decode_blocks_cover_every_chunk(rules, shift):
         for s in range(n):
             chunks = -(-int(ctx[s]) >> shift)
             assert chunks <= first[s + 1] - first[s] <= chunks + 1
+
+
+def test_decode_plan(rules):
+    def plan(ctx, fp4=0):
+        out = (ctypes.c_long * 3)()
+        rules.rows_plan(len(ctx), int(max(ctx)), ctypes.c_long(int(sum(ctx))), 256, fp4, out)
+        chunk, per_seq, blocks = out
+        assert chunk in (256, 512, 1024, 2048) and blocks < 1 << 24
+        # every chunk of every session has a block
+        assert per_seq * chunk >= max(ctx) and blocks == per_seq * len(ctx) if per_seq else \
+            blocks == sum(ctx) // chunk + len(ctx)
+        return chunk, per_seq, blocks, sum(-(-c // chunk) for c in ctx)
+    # sessions of one length: no empty block, one block per CU where that many suffice
+    assert plan([8000] * 64)[:3] == (2048, 4, 256)
+    assert plan([131073])[0] == 512 and plan([2000] * 2)[0] == 256
+    for ctx in ([4000] * 256, [1000] * 4096, [100000] * 64):
+        _, _, blocks, useful = plan(ctx)
+        assert blocks == useful
+    # one long session among short ones does not set the grid of all
+    rng = np.random.default_rng(3)
+    ragged = [[1000000] + [1000] * 63, [1000000] + [500] * 1023]
+    ragged += [[int(c) for c in np.exp(rng.uniform(7, 12.5, n))] for n in (3, 17, 64, 300, 2000) for _ in range(8)]
+    for ctx in ragged:
+        for fp4 in (0, 1):
+            _, _, blocks, useful = plan(ctx, fp4)
+            assert blocks <= 2 * useful + 16, (len(ctx), blocks, useful)
+    assert plan([1 << 24])[2] and plan([1] * 100000)[2] == 100000

@@ -38,7 +38,6 @@ namespace janus {
 
 constexpr int IDX_TPW = 2;                          // tokens per wave
 constexpr int IDX_WAVES = 4;                        // waves per block
-constexpr int IDX_KEY_CHUNK = 16384;                // target keys per block: long blocks spread each block's query and weight loads over more keys
 
 // Block tile slot -> (session, first session-local token); false past the end.
 JANUS_DEV bool tile_slot(const int32_t *q_start, int num_seqs, int slot, int tile, int &b, int &t0)
@@ -239,9 +238,6 @@ JANUS_DEV void head_group_f4(float &acc, const v8i &a0, const v8i &a1, const v8i
             : IDX_HEAD_GROUP_CLOBBERS);
 }
 
-constexpr int IDX_STAGE = 128;                      // keys per LDS stage (16 KB)
-constexpr int IDX_XCD = 8;                          // L2 domains (XCDs) of the chip
-
 typedef __attribute__((address_space(3))) void lds_void_t;
 
 // s_waitcnt immediate (gfx9 encoding) that waits for vmcnt <= n only.
@@ -270,29 +266,18 @@ JANUS_DEV float xor_lanes16(float x)
     return __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, x), 0x401F));
 }
 
-// Block id -> (token tile slot, key chunk).  Workgroups are dispatched round
-// robin over the XCDs, so block L runs on XCD L % 8; all blocks of key chunk
-// c are given to XCD c % 8, which keeps each XCD's share of the keys (about
-// 1/8 of them) resident in that XCD's L2.
-JANUS_DEV bool xcd_tile_chunk(int L, int nchunks, int ntiles, int &tile, int &chunk)
+// Block id -> (token tile slot, key chunk), per chunks of a session on each XCD.
+// Workgroups are dispatched round robin over the XCDs, so block L runs on XCD
+// L % 8; all blocks of key chunk c are given to XCD c % 8, which keeps each
+// XCD's share of the keys (about 1/8 of them) resident in that XCD's L2.
+JANUS_DEV bool xcd_tile_chunk(int L, int per, int ntiles, int &tile, int &chunk)
 {
     const int x = L % IDX_XCD, s = L / IDX_XCD;
-    const int nc = (nchunks - x + IDX_XCD - 1) / IDX_XCD;  // chunks owned by this XCD
-    if (nc <= 0 || s >= nc * ntiles)
+    if (s >= per * ntiles)
         return false;
-    tile = s / nc;
-    chunk = x + IDX_XCD * (s % nc);
+    tile = s / per;
+    chunk = x + IDX_XCD * (s % per);
     return true;
-}
-
-// Keys of one chunk of a session: its context over the launch's chunk count,
-// in whole stages.  Every session has chunks on every XCD that way; with the
-// chunk length of the longest session, a shorter one had only the first
-// chunks, so that the last XCDs idled (eight sessions of 10K to 51K tokens,
-// MXFP4 keys: 3995 -> 2998 us; sixteen of 0.5K to 131K, fp8 keys: 2948 -> 950).
-JANUS_DEV int session_chunk(int ctx, int nchunks)
-{
-    return ((ctx + nchunks - 1) / nchunks + IDX_STAGE - 1) / IDX_STAGE * IDX_STAGE;
 }
 
 // LDS stage layout: key row r (128 bytes) holds its 16-byte column c at slot
@@ -309,7 +294,7 @@ template <int H, int TPW>
 __global__ __launch_bounds__(256, (TPW == 4 ? 2 : 4)) void index_scores_fp8_mfma(
     const int32_t *__restrict__ q_start, const int32_t *__restrict__ ctx_start,
     const int32_t *__restrict__ hist_len, const int64_t *__restrict__ score_start, int num_seqs, int es,
-    int nchunks, int ntiles, const uint8_t *__restrict__ q, const float *__restrict__ q_scale,
+    int per, unsigned recip, int ntiles, const uint8_t *__restrict__ q, const float *__restrict__ q_scale,
     const uint8_t *__restrict__ kI, const float *__restrict__ k_scale, const float *__restrict__ w,
     float *__restrict__ scores)
 {
@@ -326,14 +311,14 @@ __global__ __launch_bounds__(256, (TPW == 4 ? 2 : 4)) void index_scores_fp8_mfma
     __shared__ float sKs0[IDX_STAGE];
     __shared__ float sKs1[IDX_STAGE];
     int slot, chunk, b, tile0;
-    if (!xcd_tile_chunk(blockIdx.x, nchunks, ntiles, slot, chunk))
+    if (!xcd_tile_chunk(blockIdx.x, per, ntiles, slot, chunk))
         return;
     if (!tile_slot(q_start, num_seqs, slot, TOK_TILE, b, tile0))
         return;
     const int N = q_start[b + 1] - q_start[b];
     const int M = hist_len[b];
     const int ctx = entries_of(M + N, es);
-    const int key_chunk = session_chunk(ctx, nchunks);
+    const int key_chunk = session_chunk(ctx, per, recip);
     const int key_lo = chunk * key_chunk;
     if (key_lo >= ctx)
         return;
@@ -514,7 +499,7 @@ JANUS_DEV v8bf as_v8bf(v4i x) { return __builtin_bit_cast(v8bf, x); }
 __global__ __launch_bounds__(256, 2) void index_scores_bf16_mfma(
     const int32_t *__restrict__ q_start, const int32_t *__restrict__ ctx_start,
     const int32_t *__restrict__ hist_len, const int64_t *__restrict__ score_start, int num_seqs, int es,
-    int nchunks, int ntiles, const uint16_t *__restrict__ q, const float *__restrict__ q_scale,
+    int per, unsigned recip, int ntiles, const uint16_t *__restrict__ q, const float *__restrict__ q_scale,
     const uint8_t *__restrict__ kI, const float *__restrict__ k_scale, const float *__restrict__ w,
     float *__restrict__ scores)
 {
@@ -524,14 +509,14 @@ __global__ __launch_bounds__(256, 2) void index_scores_bf16_mfma(
     __shared__ float sKs0[IDX_STAGE];
     __shared__ float sKs1[IDX_STAGE];
     int slot, chunk, b, tile0;
-    if (!xcd_tile_chunk(blockIdx.x, nchunks, ntiles, slot, chunk))
+    if (!xcd_tile_chunk(blockIdx.x, per, ntiles, slot, chunk))
         return;
     if (!tile_slot(q_start, num_seqs, slot, TOK_TILE, b, tile0))
         return;
     const int N = q_start[b + 1] - q_start[b];
     const int M = hist_len[b];
     const int ctx = entries_of(M + N, es);
-    const int key_chunk = session_chunk(ctx, nchunks);
+    const int key_chunk = session_chunk(ctx, per, recip);
     const int key_lo = chunk * key_chunk;
     if (key_lo >= ctx)
         return;
@@ -728,7 +713,7 @@ constexpr int F4_ROW = 64;  // bytes of e2m1 codes per key (128 dims)
 __global__ __launch_bounds__(256, 4) void index_scores_mxfp4_mfma(
     const int32_t *__restrict__ q_start, const int32_t *__restrict__ ctx_start,
     const int32_t *__restrict__ hist_len, const int64_t *__restrict__ score_start, int num_seqs, int es,
-    int nchunks, int ntiles, const uint8_t *__restrict__ q, const float *__restrict__ q_scale,
+    int per, unsigned recip, int ntiles, const uint8_t *__restrict__ q, const float *__restrict__ q_scale,
     const uint8_t *__restrict__ kI, const uint8_t *__restrict__ k_bscale, const float *__restrict__ k_scale,
     const float *__restrict__ w, float *__restrict__ scores)
 {
@@ -740,14 +725,14 @@ __global__ __launch_bounds__(256, 4) void index_scores_mxfp4_mfma(
     __shared__ float sKs0[IDX_STAGE];
     __shared__ float sKs1[IDX_STAGE];
     int slot, chunk, b, tile0;
-    if (!xcd_tile_chunk(blockIdx.x, nchunks, ntiles, slot, chunk))
+    if (!xcd_tile_chunk(blockIdx.x, per, ntiles, slot, chunk))
         return;
     if (!tile_slot(q_start, num_seqs, slot, TOK_TILE, b, tile0))
         return;
     const int N = q_start[b + 1] - q_start[b];
     const int M = hist_len[b];
     const int ctx = entries_of(M + N, es);
-    const int key_chunk = session_chunk(ctx, nchunks);
+    const int key_chunk = session_chunk(ctx, per, recip);
     const int key_lo = chunk * key_chunk;
     if (key_lo >= ctx)
         return;
@@ -1322,13 +1307,6 @@ __global__ __launch_bounds__(256, 2) void index_scores_rows(
 
 namespace janus {
 
-// Key chunks per session of the prefill kernels: a multiple of the XCD count,
-// so that the longest session's are at most IDX_KEY_CHUNK keys long.
-static int prefill_chunks(const janus_batch *bt)
-{
-    return IDX_XCD * std::max(1, ceil_div(ceil_div(bt->max_ctx, IDX_XCD), IDX_KEY_CHUNK));
-}
-
 // The row-tile kernel serves sessions of at most ROWS_NQ appended tokens, one
 // tile of them each.
 static int rows_nq(const janus_batch *bt) { return bt->max_q <= 1 ? 1 : bt->max_q <= 2 ? 2 : ROWS_NQ; }
@@ -1392,23 +1370,23 @@ extern "C" int janus_index_scores(const janus_batch *bt, const void *q, janus_dt
         return launch_status();
     }
     if (q_dt == JANUS_FP8_E4M3 && d == 128 && H == 64 && bt->max_ctx <= (1 << 24)) {
-        const int nchunks = prefill_chunks(bt);
+        const int per = prefill_per_xcd(bt->max_ctx);
         constexpr int TPW = IDX_TPW;
         const int ntiles = ceil_div(bt->total_q, 4 * TPW) + nseq;
-        const int per_xcd = ceil_div(nchunks, IDX_XCD) * ntiles;
-        hipLaunchKernelGGL((index_scores_fp8_mfma<64, TPW>), dim3(IDX_XCD * per_xcd), dim3(256), 0, st, bt->q_start,
-                           bt->ctx_start, bt->hist_len, bt->score_start, nseq, bt->entry_shift, nchunks, ntiles,
+        hipLaunchKernelGGL((index_scores_fp8_mfma<64, TPW>), dim3(IDX_XCD * per * ntiles), dim3(256), 0, st, bt->q_start,
+                           bt->ctx_start, bt->hist_len, bt->score_start, nseq, bt->entry_shift, per, prefill_recip(per),
+                           ntiles,
                            (const uint8_t *)q, q_scale, (const uint8_t *)kI, k_scale, w, scores);
         return launch_status();
     }
     if (q_dt == JANUS_BF16 && d == 128 && H == 64 && bt->max_ctx <= (1 << 23)) {
         // bf16 on bf16 MFMA: the fp8 kernel's key chunking (32-bit buffer
         // offsets over 256-byte key rows: contexts up to 2^23)
-        const int nchunks = prefill_chunks(bt);
+        const int per = prefill_per_xcd(bt->max_ctx);
         const int ntiles = ceil_div(bt->total_q, 8) + nseq;
-        const int per_xcd = ceil_div(nchunks, IDX_XCD) * ntiles;
-        hipLaunchKernelGGL(index_scores_bf16_mfma, dim3(IDX_XCD * per_xcd), dim3(256), 0, st, bt->q_start,
-                           bt->ctx_start, bt->hist_len, bt->score_start, nseq, bt->entry_shift, nchunks, ntiles,
+        hipLaunchKernelGGL(index_scores_bf16_mfma, dim3(IDX_XCD * per * ntiles), dim3(256), 0, st, bt->q_start,
+                           bt->ctx_start, bt->hist_len, bt->score_start, nseq, bt->entry_shift, per, prefill_recip(per),
+                           ntiles,
                            (const uint16_t *)q, q_scale, (const uint8_t *)kI, k_scale, w, scores);
         return launch_status();
     }
@@ -1442,12 +1420,11 @@ extern "C" int janus_index_scores_mxfp4(const janus_batch *bt, const void *q, co
         return launch_status();
     }
     // prefill-shaped: keys staged through LDS, the fp8 kernel's chunking
-    const int nchunks = prefill_chunks(bt);
+    const int per = prefill_per_xcd(bt->max_ctx);
     const int ntiles = ceil_div(bt->total_q, 8) + bt->num_seqs;
-    const int per_xcd = ceil_div(nchunks, IDX_XCD) * ntiles;
-    hipLaunchKernelGGL(index_scores_mxfp4_mfma, dim3(IDX_XCD * per_xcd), dim3(256), 0, as_stream(stream),
+    hipLaunchKernelGGL(index_scores_mxfp4_mfma, dim3(IDX_XCD * per * ntiles), dim3(256), 0, as_stream(stream),
                        bt->q_start, bt->ctx_start, bt->hist_len, bt->score_start, bt->num_seqs, bt->entry_shift,
-                       nchunks, ntiles, (const uint8_t *)q, q_scale, (const uint8_t *)kI, k_block_scale,
+                       per, prefill_recip(per), ntiles, (const uint8_t *)q, q_scale, (const uint8_t *)kI, k_block_scale,
                        k_scale, w, scores);
     return launch_status();
 }

@@ -29,6 +29,38 @@ constexpr bool pd_one_block(int64_t total_q, int64_t k, int nwords)
     return total_q > 0 && nwords > 0 && nwords <= RUN_THREADS && pd_steps(total_q, k) <= PD_SMALL_STEPS;
 }
 
+// ---- prefill indexer: key chunks of a session -----------------------------------
+
+constexpr int IDX_XCD = 8;            // L2 domains (XCDs) of the chip
+constexpr int IDX_STAGE = 128;        // keys per LDS stage
+constexpr int IDX_KEY_CHUNK = 16384;  // target keys per block: long blocks spread each block's query and weight loads over more keys
+
+// Chunks per XCD of every session: the longest session's are at most
+// IDX_KEY_CHUNK keys long.  Contexts up to 2^24: at most 128.
+constexpr int prefill_per_xcd(int max_ctx)
+{
+    const int per = ((max_ctx + IDX_XCD - 1) / IDX_XCD + IDX_KEY_CHUNK - 1) / IDX_KEY_CHUNK;
+    return per > 1 ? per : 1;
+}
+// ceil(2^31 / n): the division by n that session_chunk makes, as a multiplication
+constexpr unsigned prefill_recip(int n) { return ((1u << 31) + (unsigned)n - 1) / (unsigned)n; }
+
+// Keys of one chunk of a session: its context over the launch's chunk count
+// (IDX_XCD * n), in whole stages.  Every session has chunks on every XCD that
+// way; with the chunk length of the longest session, a shorter one had only the
+// first chunks, so that the last XCDs idled (eight sessions of 10K to 51K
+// tokens, MXFP4 keys: 3995 -> 2998 us; sixteen of 0.5K to 131K, fp8 keys: 2948
+// -> 950).  x = ceil(ctx / 8) + n - 1 is below 2^22 and the reciprocal's error
+// below n <= 2^7 in 2^31, so that x * recip >> 31 is the exact quotient: a
+// block's first loads wait for it, and the division made an append of 5 to 200
+// tokens 1% slower than no division (47.9 against 47.4 us at 16K tokens).
+constexpr int session_chunk(int ctx, int n, unsigned recip)
+{
+    const unsigned x = (unsigned)((ctx + IDX_XCD - 1) / IDX_XCD + n - 1);
+    const int keys = (int)((unsigned long long)x * recip >> 31);
+    return (keys + IDX_STAGE - 1) / IDX_STAGE * IDX_STAGE;
+}
+
 // ---- decode indexer: blocks of a batch ----------------------------------------
 
 // First block of session s, whose keys start at ctx_start, in chunks of 2^shift

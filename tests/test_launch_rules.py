@@ -12,6 +12,8 @@ WRAP = r"""
 #include "launch_rules.hpp"
 extern "C" {
 int pd_one_block(long q, long k, int nwords) { return janus::pd_one_block(q, k, nwords); }
+int prefill_per_xcd(int max_ctx) { return janus::prefill_per_xcd(max_ctx); }
+int session_chunk(int ctx, int n) { return janus::session_chunk(ctx, n, janus::prefill_recip(n)); }
 void rows_plan(int n, int max_ctx, long total, int cus, int fp4, long *out)
 {
     const janus::RowsPlan p = janus::rows_plan(n, max_ctx, total, cus, fp4);
@@ -79,3 +81,14 @@ def test_decode_plan(rules):
             _, _, blocks, useful = plan(ctx, fp4)
             assert blocks <= 2 * useful + 16, (len(ctx), blocks, useful)
     assert plan([1 << 24])[2] and plan([1] * 100000)[2] == 100000
+
+
+def test_prefill_chunks(rules):
+    rng = np.random.default_rng(5)
+    assert rules.prefill_per_xcd(1) == 1 and rules.prefill_per_xcd(131072) == 1 and rules.prefill_per_xcd(131073) == 2
+    assert rules.prefill_per_xcd(1 << 24) == 128
+    for n in list(range(1, 129)):
+        for ctx in [0, 1, 7, 8, 9, 8 * n, 8 * n + 1, 1 << 24, (1 << 24) - 1] + list(rng.integers(1, 1 << 24, 200)):
+            ctx = int(ctx)
+            keys = -(-ctx // (8 * n))
+            assert rules.session_chunk(ctx, n) == -(-keys // 128) * 128, (ctx, n)

@@ -122,4 +122,18 @@ constexpr RowsPlan rows_plan(int num_seqs, int max_ctx, int64_t total_ctx, int c
     return best;
 }
 
+// ---- top-k: the sample that seeds a row's threshold ----------------------------
+
+constexpr int TK_SAMPLE_GROUPS = 512;  // ~1/32 of a 128K row, in 8-element groups
+
+// Group of a row of ngroups groups that is the sample's g-th, over the whole
+// row.  A whole stride (ngroups / TK_SAMPLE_GROUPS) left out up to half of a
+// short row, its end, and a row with its high scores ahead of that was streamed
+// again: 512 rows of 8184 descending scores (k = 512) 31.3 us, now 10.9.
+// (ngroups <= 2^16 by the launcher's bound on contexts: the product fits.)
+constexpr int tk_sample_group(int g, int ngroups)
+{
+    return ngroups <= TK_SAMPLE_GROUPS ? g : (int)((unsigned)g * (unsigned)ngroups / TK_SAMPLE_GROUPS);
+}
+
 } // namespace janus

@@ -5,11 +5,11 @@
 // One block per row.  A row (up to 557 KB at a 128K history) does not fit in
 // LDS, so the block streams it from HBM once, keeping only candidates that
 // beat a running threshold in an LDS buffer of CAP (key, id) pairs:
-//   1. threshold seed: a strided sample of 8-element groups (1/32 of a 128K
-//      row) gives the key of a rank a little above k * (sample share), so that
-//      in expectation ~1.3k elements pass.  (Whole 128-byte lines, four times as
-//      far apart, hit spans of high scores too unevenly: a row whose seed came
-//      out above its k-th key is streamed again);
+//   1. threshold seed: a sample of 8-element groups spread over the row (1/32
+//      of a 128K row) gives the key of a rank a little above k * (sample
+//      share), so that in expectation ~1.3k elements pass.  (Whole 128-byte
+//      lines, four times as far apart, hit spans of high scores too unevenly: a
+//      row whose seed came out above its k-th key is streamed again);
 //   2. streaming filter: each wave takes 1 KB chunks of its own, TK_RING of
 //      them in flight in registers, and appends what it accepts with one LDS
 //      atomic per chunk that has any.  The waves meet only when the row is
@@ -37,6 +37,7 @@
 // rows of 8.2K (k = 512) 90 -> 50.
 #include "janus_device.hpp"
 #include "janus_host.hpp"
+#include "launch_rules.hpp"
 
 #include <algorithm>
 #include <type_traits>
@@ -46,7 +47,6 @@ namespace janus {
 constexpr int TK_RING = 8;                // 1 KB chunks in flight per wave
 constexpr int TK_MAX_K = 6144;            // with CAP = 8192: >= 2048 free slots after a cut
 constexpr int TK_SMALL_K = 2048;          // with CAP = 4096
-constexpr int TK_SAMPLE_GROUPS = 512;     // ~1/32 of a 128K row, in 8-element groups
 constexpr int TK_BINS = 2048;
 constexpr int TK_FEW = 64;                // entries of a bin that are ranked pairwise
 
@@ -384,13 +384,12 @@ JANUS_DEV void stream_row(TopkShared<TPB, CAP> &sm, const float *__restrict__ ro
     // wave's first chunks; the sample is ranked under their latency
     constexpr int SPT = TK_SAMPLE_GROUPS * 2 / TPB;  // float4s of the sample per thread
     const int ngroups = nbody4 >> 1;
-    const int stride = max(1, ngroups / TK_SAMPLE_GROUPS);
     const int m4 = seed > 0.f ? min(TK_SAMPLE_GROUPS, ngroups) * 2 : 0;
     v4f smp[SPT];
 #pragma unroll
     for (int j = 0; j < SPT; ++j) {
         const int e = (int)threadIdx.x + j * TPB;
-        smp[j] = load4(e < m4 ? (e >> 1) * stride * 2 + (e & 1) : nbody4);
+        smp[j] = load4(e < m4 ? 2 * tk_sample_group(e >> 1, ngroups) + (e & 1) : nbody4);
     }
     // lanes 0..2 of the first wave take the head, 4..6 the tail
     const int hti = lane < 4 ? lane : tail0 + lane - 4;
@@ -461,7 +460,10 @@ JANUS_DEV void stream_row(TopkShared<TPB, CAP> &sm, const float *__restrict__ ro
 }
 
 // After a seed above the k-th key: the row again with a looser seed, then with
-// none.  Begins with a barrier.
+// none.  Begins with a barrier.  512 rows of 131K: 65 us with the first seed,
+// 91 with the second, 132 where the sample misleads both (two streams, the
+// second without a threshold, would be one less, but the streams that filter
+// are the cheap ones, and with one seed alone the middle case took the last's).
 template <int TPB, int CAP>
 __device__ __noinline__ void stream_again(TopkShared<TPB, CAP> &sm, const float *row, int n, int k)
 {

@@ -131,13 +131,15 @@ FILLS = {
 
 
 def _sample_trap(rng, n):
-    """High values exactly where a strided sample of 32-element lines looks
-    (8 per sampled line), too few to fill k: a threshold taken from such a
+    """High values exactly where the threshold's sample looks (three in each
+    of the 512 groups of 8 elements spread over the row, wherever in 16 bytes
+    the row starts), too few to fill k = 2048: a threshold taken from the
     sample sits above the k-th score, which the kernel must detect."""
-    stride = max(1, (n >> 5) // 128)
-    idx = np.arange(n)
-    hot = ((idx >> 5) % stride == 0) & ((idx & 31) < 8)
-    return rng.random(n) + np.where(hot, 10.0, 0.0)
+    ng = n >> 3
+    g = np.arange(min(ng, 512)) * max(ng, 512) // 512
+    r = rng.random(n)
+    r[(8 * g[:, None] + np.arange(3, 6)).reshape(-1)] += 10.0
+    return r
 
 
 @pytest.mark.parametrize("fill", list(FILLS))

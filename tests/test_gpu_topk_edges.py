@@ -38,3 +38,45 @@ def test_topk_edges(fill, hist, new, k):
         want = min(k, hist + i + 1)
         assert np.all(got[i, want:] == -1) and np.all(np.diff(got[i, :want]) > 0)
         assert np.array_equal(got[i, :want], np.sort(ref[i, :want])), (fill, i)
+
+
+def _sampled(row):
+    """The scores of the seed's sample in a 16-byte aligned row: 512 groups of 8 spread over it."""
+    ng = len(row) >> 3
+    g = np.arange(512) * ng // 512
+    return (8 * g[:, None] + np.arange(8)).reshape(-1)
+
+
+def _passes(row, k, seed):
+    """Fewest and most elements that a threshold from the sample can let through: the lower
+    end of a narrow range of values around the sample's rank."""
+    s = np.sort(row[_sampled(row)])[::-1]
+    r = int(np.float32(seed) * k * len(s) / len(row)) + 8
+    return int((row >= s[r - 1]).sum()), int((row >= s[min(len(s), r + max(4, r >> 3) + 1) - 1]).sum())
+
+
+@pytest.mark.parametrize("k", [1000, 2048])
+@pytest.mark.parametrize("ctx", [40000, 131072, 262400])
+@pytest.mark.parametrize("misses", [1, 2])
+def test_seed_misses(ctx, misses, k):
+    """High scores exactly in the sample, too few to fill k: the first threshold (misses = 1) or
+    the looser second one too (misses = 2) lies above the k-th score, and the row is streamed again."""
+    new = 4
+    rng = np.random.default_rng(ctx + k)
+    rows = np.full((new, ctx), -np.inf, np.float32)
+    for i in range(new):
+        n = ctx - new + i + 1
+        rows[i, :n] = rng.random(n)
+        at = _sampled(rows[i, :n])
+        h = int((1.25 if misses == 1 else 3.5) * 1.3 * k * len(at) / n) + 12 * misses
+        assert h < k
+        rows[i, rng.choice(at, h, replace=False)] += 10
+        lo, hi = _passes(rows[i, :n], k, 1.3)
+        assert hi < k
+        lo, hi = _passes(rows[i, :n], k, 3.0)
+        assert hi < k if misses == 2 else k <= lo
+    bt = janus.Batch([ctx - new], [new])
+    sel = janus.topk(bt, torch.from_numpy(rows.reshape(-1)).cuda(), k)
+    torch.cuda.synchronize()
+    ref = oracle.topk([0, new], [ctx - new], np.arange(new), rows, k)
+    assert np.array_equal(sel.cpu().numpy(), np.sort(ref, axis=1))

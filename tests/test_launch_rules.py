@@ -19,6 +19,7 @@ void rows_plan(int n, int max_ctx, long total, int cus, int fp4, long *out)
     const janus::RowsPlan p = janus::rows_plan(n, max_ctx, total, cus, fp4);
     out[0] = p.chunk, out[1] = p.per_seq, out[2] = p.blocks;
 }
+int tk_sample_group(int g, int ngroups) { return janus::tk_sample_group(g, ngroups); }
 int rows_first(int ctx_start, int s, int shift) { return janus::rows_first(ctx_start, s, shift); }
 }
 """
@@ -92,3 +93,11 @@ def test_prefill_chunks(rules):
             ctx = int(ctx)
             keys = -(-ctx // (8 * n))
             assert rules.session_chunk(ctx, n) == -(-keys // 128) * 128, (ctx, n)
+
+
+def test_topk_sample_spans_the_row(rules):
+    for n in list(range(513)) + [1022, 1023, 1024, 1025, 2047, 5000, 16384, 65535, 1 << 16]:
+        g = [rules.tk_sample_group(j, n) for j in range(min(n, 512))]
+        assert g == sorted(set(g)) and (not g or g[0] == 0 and g[-1] < n)
+        # no stretch of the row longer than one and a half shares is left out, the end neither
+        assert all(b - a <= 1.5 * n / 512 + 1 for a, b in zip(g, g[1:] + [n]))

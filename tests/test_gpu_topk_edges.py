@@ -40,6 +40,22 @@ def test_topk_edges(fill, hist, new, k):
         assert np.array_equal(got[i, :want], np.sort(ref[i, :want])), (fill, i)
 
 
+@pytest.mark.parametrize("ctx,k", [(5000, 2048), (40000, 1000), (131072, 2048), (131072, 2)])
+@pytest.mark.parametrize("levels", [1, 2, 50])
+def test_ties_below_outliers(ctx, k, levels):
+    """Few scores far above the rest, which lie on one or some neighbouring values: the first
+    range narrowing puts them into one bin, the next ones onto one bin again or side by side."""
+    rng = np.random.default_rng(ctx + levels)
+    row = (1 + rng.integers(0, levels, ctx) * 2.0 ** -23).astype(np.float32)
+    high = rng.random(ctx) < 0.002
+    row[high] = 10.0 ** rng.uniform(1, 30, int(high.sum()))
+    bt = janus.Batch([ctx - 1], [1])
+    sel = janus.topk(bt, torch.from_numpy(row).cuda(), k)
+    torch.cuda.synchronize()
+    ref = oracle.topk([0, 1], [ctx - 1], [0], row[None], k)
+    assert np.array_equal(sel.cpu().numpy(), np.sort(ref, axis=1))
+
+
 def _sampled(row):
     """The scores of the seed's sample in a 16-byte aligned row: 512 groups of 8 spread over it."""
     ng = len(row) >> 3

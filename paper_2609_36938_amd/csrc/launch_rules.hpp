@@ -136,4 +136,25 @@ constexpr int tk_sample_group(int g, int ngroups)
     return ngroups <= TK_SAMPLE_GROUPS ? g : (int)((unsigned)g * (unsigned)ngroups / TK_SAMPLE_GROUPS);
 }
 
+// ---- MQA attention: one token per wave, or the block's waves on one token ------
+
+constexpr int MQA_WAVES = 4;  // waves per block
+
+// Whether a block's four waves share one token.  A batch takes rounds of one
+// block per CU, of which the whole chip has 256 (asking the device took 0.4 of
+// the 12 us of a small call, and a part of a chip only gets the slower form).
+// One round's time in ns, fitted to 270 batches of 8 to 6000 rows of 32 to 1024
+// ids with 1, 8 and 16 heads (which differ by 5%): 3400 + 12 k for a shared
+// token, 3800 + 49 k for four.  The rule takes the faster form of all of them to
+// within 2% (256 ids: 500 rows 13.8 us shared, 18.6 else, 768 rows 19.5 and 19.1;
+// 512 ids: 1024 rows 39 and 31, 1100 rows 46 and 58).  Up to 100 ids, three or
+// four tiles for four waves, the forms take as long as each other in one round,
+// and longer batches keep a token per wave.
+constexpr bool mqa_shared(int64_t total_q, int64_t k)
+{
+    const int64_t one = (total_q + 255) / 256;
+    const int64_t four = (total_q + 256 * MQA_WAVES - 1) / (256 * MQA_WAVES);
+    return k > 100 && one * (3400 + 12 * k) < four * (3800 + 49 * k);
+}
+
 } // namespace janus

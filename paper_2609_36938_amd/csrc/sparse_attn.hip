@@ -22,6 +22,7 @@
 //   * O accumulates in fp32 MFMA accumulators and is normalised at the end.
 #include "janus_device.hpp"
 #include "janus_host.hpp"
+#include "launch_rules.hpp"
 
 #include <algorithm>
 #include <mutex>
@@ -1345,7 +1346,6 @@ constexpr int MQA_D = 128;                     // dqk = dv
 constexpr int MQA_ROWB = MQA_D * 2;            // bytes per K or V row
 constexpr int MQA_TILEB = MLA_KT * MQA_ROWB;   // one 32-row tile (8 KB)
 constexpr int MQA_MAX_K = 1024;                // selected ids per token held in LDS
-constexpr int MQA_WAVES = 4;                   // tokens per block
 
 // SHARED: the four waves share one token, wave w taking tiles w, w + 4, .., and
 // are merged through LDS at the end, so that a quarter of a token's tiles run
@@ -1757,17 +1757,6 @@ static bool mqa_shape(const void *q, int Hq, int dqk, int dv, const void *k_pool
            (v_row_stride % 8) == 0 && k_row_stride <= (1 << 30) && v_row_stride <= (1 << 30) &&
            (reinterpret_cast<uintptr_t>(k_pool) & 15) == 0 && (reinterpret_cast<uintptr_t>(v_pool) & 15) == 0 &&
            (reinterpret_cast<uintptr_t>(q) & 15) == 0;
-}
-
-// Whether a block's waves share one token: the batch's time in rounds of one
-// block per CU (256 of them), from rounds measured at 8 heads, in ns: 8000 + 9 k
-// with one token per block (10.3 us at k = 256, 17.3 at 1024), 3900 + 50 k with
-// four (16.7 and 55.1).
-static bool mqa_shared(int total_q, int k)
-{
-    const int64_t one = (int64_t)ceil_div(total_q, 256) * (8000 + 9 * k);
-    const int64_t four = (int64_t)ceil_div(total_q, 256 * MQA_WAVES) * (3900 + 50 * k);
-    return one < four;
 }
 
 // one launch of the MLA kernel: splits blocks per token, each over one slice

@@ -20,7 +20,7 @@ def T(a):
 
 @pytest.mark.parametrize("Hq,k,new,scale", [(8, 256, [256], 0.088), (1, 1, [3, 2], 0.088), (16, 31, [5, 1], 1.0),
                                             (5, 129, [9], 1.0), (8, 128, [4], 1.0), (16, 1024, [6, 250], 1.0),
-                                            (8, 129, [257], 1.0), (3, 700, [200, 61], 0.088)])
+                                            (8, 129, [257], 1.0), (16, 300, [800, 220], 1.0), (3, 700, [200, 61], 0.088)])
 def test_mqa(Hq, k, new, scale):
     attn = dict(Hq=Hq, dqk=128, dv=128, mla=False, q_std=1.0, kv_std=1.0, scale=scale)
     wl = make_workload(hist_len=[1800, 100][:len(new)], new_len=new, H=2, d=8, idx_dtype="f32", k=k, seed=21 + Hq,

@@ -20,6 +20,7 @@ void rows_plan(int n, int max_ctx, long total, int cus, int fp4, long *out)
     out[0] = p.chunk, out[1] = p.per_seq, out[2] = p.blocks;
 }
 int tk_sample_group(int g, int ngroups) { return janus::tk_sample_group(g, ngroups); }
+int mqa_shared(long q, long k) { return janus::mqa_shared(q, k); }
 int rows_first(int ctx_start, int s, int shift) { return janus::rows_first(ctx_start, s, shift); }
 }
 """
@@ -101,3 +102,15 @@ def test_topk_sample_spans_the_row(rules):
         assert g == sorted(set(g)) and (not g or g[0] == 0 and g[-1] < n)
         # no stretch of the row longer than one and a half shares is left out, the end neither
         assert all(b - a <= 1.5 * n / 512 + 1 for a, b in zip(g, g[1:] + [n]))
+
+
+def test_mqa_shared(rules):
+    def shared(q, k):
+        return bool(rules.mqa_shared(ctypes.c_long(q), ctypes.c_long(k)))
+    # measured: one token per block faster, then one token per wave
+    for q, k in [(8, 256), (250, 256), (500, 256), (512, 256), (1100, 256), (260, 512), (520, 512), (1100, 512),
+                 (2100, 512), (256, 1024), (768, 1024), (1100, 1024), (1500, 1024), (2100, 1024)]:
+        assert shared(q, k), (q, k)
+    for q, k in [(1000, 32), (6000, 32), (1000, 100), (2048, 100), (1000, 256), (1500, 256), (3000, 256), (1024, 512),
+                 (2048, 512), (4096, 512), (1000, 1024), (2048, 1024), (3000, 1024)]:
+        assert not shared(q, k), (q, k)

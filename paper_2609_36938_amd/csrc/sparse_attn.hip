@@ -479,29 +479,27 @@ __global__ __launch_bounds__(64 * NW, 1) void sparse_mla_mfma(
             issue_group(std::integral_constant<int, I0>{}, std::integral_constant<int, I1>{}, t, dst);
     };
 
-    // ---- bf16 rows: wave w gathers main rows MROWS*w .. MROWS*w+MROWS-1
-    // (one instruction each: a wave-uniform source row, its slot taken from
-    // a register of prefetched slots) and tail blocks m = w + NW*u < 4
+    // ---- bf16 rows (eight waves: sparse_mla_few has fewer heads): wave w
+    // gathers main rows MROWS*w .. MROWS*w+MROWS-1 (one instruction each: a
+    // wave-uniform source row, its slot taken from a register of prefetched
+    // slots) and, w < 4, tail block w
+    static_assert(KV8 || NW == 8, "bf16 rows come with 128 heads here");
     constexpr int MROWS = MLA_KT / NW;
-    constexpr int NTAIL = NW >= 4 ? 1 : 4 / NW;
-    const bool has_tail = wave < 4;  // (every wave when NW <= 4)
+    const bool has_tail = wave < 4;
     // the row and chunk tail block m's lane loads
     auto tail_rc = [&](int m, int ln, int &r, int &cc) {
         cc = (ln >> 3) ^ m;
         r = 8 * m + ((ln & 7) ^ cc);
     };
-    // slots of tile tt: lane l < 32 (and l - 32) holds row l's, ts[u] the
-    // one of the row this lane loads in tail block wave + NW*u
-    auto read_slots = [&](int tt, int &vs, int (&ts)[NTAIL]) {
+    // slots of tile tt: lane l < 32 (and l - 32) holds row l's, ts the one of
+    // the row this lane loads in the wave's tail block
+    auto read_slots = [&](int tt, int &vs, int &ts) {
         int ln = lane;
         asm volatile("" : "+v"(ln));
         vs = sSlot[min(MLA_KT * tt + (ln & 31), kl - 1)];
-#pragma unroll
-        for (int u = 0; u < NTAIL; ++u) {
-            int r, cc;
-            tail_rc(min(wave + NW * u, 3), ln, r, cc);
-            ts[u] = sSlot[min(MLA_KT * tt + r, kl - 1)];
-        }
+        int r, cc;
+        tail_rc(min(wave, 3), ln, r, cc);
+        ts = sSlot[min(MLA_KT * tt + r, kl - 1)];
     };
     // main row i of this wave for tile tt
     auto fire_main = [&](int i, int tt, int vs, uint8_t *__restrict__ dst) {
@@ -514,31 +512,27 @@ __global__ __launch_bounds__(64 * NW, 1) void sparse_mla_mfma(
         const uint8_t *src = kv + (uint64_t)(uint32_t)sl * (uint32_t)row_bytes + 16 * ln;
         gather16(src, dst + r * MLA_ROWB);
     };
-    auto fire_tails = [&](int tt, const int (&ts)[NTAIL], uint8_t *__restrict__ dst) {
+    auto fire_tail = [&](int tt, int ts, uint8_t *__restrict__ dst) {
         int ln = lane;
         asm volatile("" : "+v"(ln));
-#pragma unroll
-        for (int u = 0; u < NTAIL; ++u) {
-            const int m = wave + NW * u;
-            int r, cc;
-            tail_rc(m, ln, r, cc);
-            const int sl = (MLA_KT * tt + r < kl && ts[u] >= 0) ? ts[u] : 0;
-            const uint8_t *src = kv + (uint64_t)(uint32_t)sl * (uint32_t)row_bytes + 16 * (64 + cc);
-            gather16(src, dst + MLA_TAIL + 1024 * m);
-        }
+        int r, cc;
+        tail_rc(wave, ln, r, cc);
+        const int sl = MLA_KT * tt + r < kl ? max(ts, 0) : 0;
+        const uint8_t *src = kv + (uint64_t)(uint32_t)sl * (uint32_t)row_bytes + 16 * (64 + cc);
+        gather16(src, dst + MLA_TAIL + 1024 * wave);
     };
     // all of tile tt's gathers at once (the first two tiles)
     auto issue_all = [&](int tt, uint8_t *__restrict__ dst) {
         if constexpr (KV8) {
             issue(tt, 0, IPW, dst);
         } else {
-            int vs, ts[NTAIL];
+            int vs, ts;
             read_slots(tt, vs, ts);
 #pragma unroll 1
             for (int i = 0; i < MROWS; ++i)
                 fire_main(i, tt, vs, dst);
             if (has_tail)
-                fire_tails(tt, ts, dst);
+                fire_tail(tt, ts, dst);
         }
     };
     // wait until this wave's gathers of the tile before the newest one
@@ -549,14 +543,14 @@ __global__ __launch_bounds__(64 * NW, 1) void sparse_mla_mfma(
         else if constexpr (KV8)
             __builtin_amdgcn_s_waitcnt(vmcnt_only(IPW));
         else if (has_tail)
-            __builtin_amdgcn_s_waitcnt(vmcnt_only(MROWS + NTAIL));
+            __builtin_amdgcn_s_waitcnt(vmcnt_only(MROWS + 1));
         else
             __builtin_amdgcn_s_waitcnt(vmcnt_only(MROWS));
     };
     // issue point q (0..4) inside tile t's S loop, for the gathers of tile
-    // t+2: bf16 main rows in four parts, then the tails; fp8 in five groups
+    // t+2: bf16 main rows in four parts, then the tail; fp8 in five groups
     // (with eight waves one instruction each) or all at point 0
-    auto issue_part = [&](int t, int part, int vs, const int (&ts)[NTAIL], uint8_t *__restrict__ dst) {
+    auto issue_part = [&](int t, int part, int vs, int ts, uint8_t *__restrict__ dst) {
         if (t + 2 >= ntiles)
             return;
         if constexpr (KV8) {
@@ -577,17 +571,14 @@ __global__ __launch_bounds__(64 * NW, 1) void sparse_mla_mfma(
             for (int i = part * MROWS / 4; i < (part + 1) * MROWS / 4; ++i)
                 fire_main(i, t + 2, vs, dst);
         } else if (has_tail) {
-            fire_tails(t + 2, ts, dst);
+            fire_tail(t + 2, ts, dst);
         }
     };
     auto tile_step = [&](int t, const uint8_t *__restrict__ tile, uint8_t *__restrict__ next) {
         // slots of tile t+2's gathers (bf16), read now so that their LDS
         // latency passes under the first K-steps (rows past the selection
         // read a clamped slot and are redirected when their gather fires)
-        int vs = 0, ts[NTAIL];
-#pragma unroll
-        for (int u = 0; u < NTAIL; ++u)
-            ts[u] = 0;
+        int vs = 0, ts = 0;
         if constexpr (!KV8)
             read_slots(t + 2, vs, ts);
         int vslot;
@@ -945,8 +936,8 @@ __global__ __launch_bounds__(64 * NW, 1) void sparse_mla_mfma(
 // its own softmax state and all 512 output dims (128 registers), so that no P
 // is exchanged and only the hand-over of a tile shared by a group's waves
 // needs a barrier (none with one head block).  The groups are merged once per
-// row, through LDS.  A group's ring has RING tiles; all of them and the slots
-// fill the 160 KB.  16 and 32 heads take four groups of 16-key tiles, whose
+// row, through LDS.  A group has two tile buffers, one gathered while the other is
+// used; all of them and the slots fill the 160 KB.  16 and 32 heads take four groups of 16-key tiles, whose
 // P V runs on the 16-key MFMA at half its 32-key rate: MFMA time does not
 // bound them.  64 heads take two groups of 32-key tiles (864 us with the
 // former).  With 128 heads the waves' own reads of K and V (each all of them)
@@ -999,10 +990,9 @@ __global__ __launch_bounds__(512, 2) void sparse_mla_few(
 {
     constexpr int NG = few_groups<HB>(), NW = HB * NG, NT = 64 * NW, HQ = 16 * HB;
     constexpr int KT = few_kt<HB>(), KB = KT / 16, TILEB = KT * 1152, TAIL = KT * 1024;
-    constexpr int RING = FEW_RING_BYTES / (NG * TILEB);
-    constexpr int ROWS = KT / HB;                           // main rows a wave gathers per tile
-    constexpr int TAILS = KT / 8, NTAIL = (TAILS + HB - 1) / HB;  // tail blocks, and a wave's (of the first TAILS waves)
-    static_assert(RING >= 2 && RING * NG * TILEB == FEW_RING_BYTES, "the tiles fill the ring");
+    constexpr int ROWS = KT / HB;         // main rows a wave gathers per tile
+    constexpr int NTAIL = KT / 8 / HB;    // and tail blocks
+    static_assert(2 * NG * TILEB == FEW_RING_BYTES && NTAIL * 8 * HB == KT, "two buffers a group, whole shares");
     __shared__ __attribute__((aligned(16))) uint8_t sTile[FEW_RING_BYTES];
     __shared__ int32_t sSlot[MLA_MAX_K];
     const int g = SPLIT ? blockIdx.x / num_splits : blockIdx.x;
@@ -1040,11 +1030,10 @@ __global__ __launch_bounds__(512, 2) void sparse_mla_few(
     float m = M_INIT, lsum = 0.f;  // head c16 of the block
     const int ntiles = (kl + KT - 1) / KT;
     const int nsteps = (ntiles + NG - 1) / NG;
-    uint8_t *ring = sTile + grp_k * RING * TILEB;
-    const bool has_tail = hb < TAILS;
+    uint8_t *ring = sTile + grp_k * 2 * TILEB;
 
     // this wave's share of the gather of its group's tile at step s (a tile
-    // past the selection gathers row 0, so that the counts stay fixed)
+    // past the selection gathers row 0)
     const uint32_t rb = (uint32_t)row_bytes;
     const uint32_t ring_lds = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void *)ring);
     // an opaque copy of the lane index: what is derived from it is made
@@ -1060,14 +1049,13 @@ __global__ __launch_bounds__(512, 2) void sparse_mla_few(
     // slots of step s: lane l holds row l % KT's, and tail[u] the one of the
     // row that this lane loads in tail block mb: lane l fills slot
     // l = 8*(cc ^ (mb & 1)) + (i ^ cc) of the block with chunk cc of row 8*mb + i
-    auto tail_block = [&](int u) { return HB >= TAILS ? hb % TAILS : NTAIL * hb + u; };
     auto read_slots = [&](int s, Slots &v) {
         const int k0 = KT * (s * NG + grp_k), ln = lane_copy(), r = ln & (KT - 1);
         int x = sSlot[min(k0 + r, kl - 1)];
         v.main = k0 + r < kl ? max(x, 0) : 0;  // padding rows read a real row; their logits are masked
 #pragma unroll
         for (int u = 0; u < NTAIL; ++u) {
-            const int mb = tail_block(u), cc = (ln >> 3) ^ (mb & 1), rt = 8 * mb + ((ln & 7) ^ cc);
+            const int mb = NTAIL * hb + u, cc = (ln >> 3) ^ (mb & 1), rt = 8 * mb + ((ln & 7) ^ cc);
             x = sSlot[min(k0 + rt, kl - 1)];
             v.tail[u] = k0 + rt < kl ? max(x, 0) : 0;
         }
@@ -1076,13 +1064,11 @@ __global__ __launch_bounds__(512, 2) void sparse_mla_few(
         const int r = ROWS * hb + i;
         const uint32_t sl = (uint32_t)__builtin_amdgcn_readlane(v.main, r);
         gather16_row(kv + (uint64_t)sl * rb, (16u * lane_copy()) ^ (16u * few_swz(r)),
-                     ring_lds + (uint32_t)((s % RING) * TILEB + 1024 * r));
+                     ring_lds + (uint32_t)((s & 1) * TILEB + 1024 * r));
     };
     auto fire_tail = [&](int s, int u, const Slots &v) {
-        if (!has_tail)
-            return;
-        const int mb = tail_block(u), cc = (lane_copy() >> 3) ^ (mb & 1);
-        gather16(kv + (uint64_t)(uint32_t)v.tail[u] * rb + 16 * (64 + cc), ring + (s % RING) * TILEB + TAIL + 1024 * mb);
+        const int mb = NTAIL * hb + u, cc = (lane_copy() >> 3) ^ (mb & 1);
+        gather16(kv + (uint64_t)(uint32_t)v.tail[u] * rb + 16 * (64 + cc), ring + (s & 1) * TILEB + TAIL + 1024 * mb);
     };
     auto issue = [&](int s) {
         Slots v;
@@ -1094,23 +1080,13 @@ __global__ __launch_bounds__(512, 2) void sparse_mla_few(
         for (int u = 0; u < NTAIL; ++u)
             fire_tail(s, u, v);
     };
-    // this wave's gathers have landed up to those of the newest `pend` steps
-    auto wait_steps = [&](int pend) {
-        constexpr int IPW = ROWS + NTAIL;
-        if (pend <= 0)
-            __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
-        else if (pend == 1)
-            has_tail ? __builtin_amdgcn_s_waitcnt(vmcnt_only(IPW)) : __builtin_amdgcn_s_waitcnt(vmcnt_only(ROWS));
-        else
-            has_tail ? __builtin_amdgcn_s_waitcnt(vmcnt_only(2 * IPW)) : __builtin_amdgcn_s_waitcnt(vmcnt_only(2 * ROWS));
-    };
     // K operands in flight ahead of their MFMA, and V operands read before the softmax
     constexpr int KAHEAD = 4 / KB + 1, VAHEAD = 8 / KB;
-    // computes step s; with NEXT, step s + RING - 1's gathers go out among its MFMAs
+    // computes step s; with NEXT, step s + 1's gathers go out among its MFMAs
     auto compute = [&](int s, auto nextc) {
         constexpr bool NEXT = decltype(nextc)::value;
-        const int k0 = KT * (s * NG + grp_k), sn = s + RING - 1;
-        const uint8_t *tile = ring + (s % RING) * TILEB;
+        const int k0 = KT * (s * NG + grp_k), sn = s + 1;
+        const uint8_t *tile = ring + (s & 1) * TILEB;
         Slots nv;
         if constexpr (NEXT)
             read_slots(sn, nv);
@@ -1242,14 +1218,12 @@ __global__ __launch_bounds__(512, 2) void sparse_mla_few(
     // not count the gathers), and every slot is written
     __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
     __syncthreads();
-#pragma unroll
-    for (int s = 0; s < RING - 1; ++s)
-        if (s < nsteps)
-            issue(s);
-    // step s's tile is whole, and the tile before it has been read by all of
+    if (nsteps > 0)
+        issue(0);
+    // the step's tile is whole, and the tile before it has been read by all of
     // the group's waves (one wave: by itself)
-    auto arrive = [&](int s) {
-        wait_steps(min(RING - 2, nsteps - 1 - s));
+    auto arrive = [&]() {
+        __builtin_amdgcn_s_waitcnt(vmcnt_only(0));
         if constexpr (HB > 1) {
             lds_barrier();
         } else {
@@ -1258,19 +1232,19 @@ __global__ __launch_bounds__(512, 2) void sparse_mla_few(
         }
     };
     int s = 0;
-    for (; s + RING - 1 < nsteps; ++s) {
-        arrive(s);
+    for (; s + 1 < nsteps; ++s) {
+        arrive();
         compute(s, std::true_type{});
     }
-    // the last steps have nothing left to gather, and at the very last one
-    // the last groups may have no tile
+    // the last step has nothing left to gather, and in it the last groups may
+    // have no tile
     const int own = ntiles > grp_k ? (ntiles - grp_k + NG - 1) / NG : 0;
     for (; s < own; ++s) {
-        arrive(s);
+        arrive();
         compute(s, std::false_type{});
     }
     if (s < nsteps)
-        arrive(s);
+        arrive();
 
     // merge of the key groups: each group's O scaled to the head's common max,
     // summed in FEW_DIMS-wide rounds through LDS (over the tiles and slots)

@@ -191,10 +191,9 @@ JANUS_DEV void run_scan2(int32_t *s, int32_t *t, int &a, int unit_a, OpA op_a, i
 
 // Run starts among the pages of word w (bits v), and their pieces emitted: a
 // maximal run of set pages is cut from its low end into pieces of max_run.
-// last_zero: the last unset page before the word; first_zero(w): the first
-// unset page after word w.
-template <class FirstZero, class Emit>
-JANUS_DEV int run_starts(int w, uint32_t v, int last_zero, int max_run, FirstZero first_zero, Emit emit)
+// last_zero: the last unset page before the word.
+template <class Emit>
+JANUS_DEV int run_starts(int w, uint32_t v, int last_zero, int max_run, Emit emit)
 {
     int n = 0;
     while (v) {
@@ -226,11 +225,10 @@ JANUS_DEV int run_starts(int w, uint32_t v, int last_zero, int max_run, FirstZer
 // Run starts among the pages of word w: run_starts' count.  With max_run >= 32
 // a word's runs have one start each, but the one that began before the word,
 // which has one at most.
-template <class FirstZero>
-JANUS_DEV int count_starts(int w, uint32_t v, int last_zero, int max_run, FirstZero first_zero)
+JANUS_DEV int count_starts(int w, uint32_t v, int last_zero, int max_run)
 {
     if (max_run < 32)
-        return run_starts(w, v, last_zero, max_run, first_zero, [](int, int, int) {});
+        return run_starts(w, v, last_zero, max_run, [](int, int, int) {});
     int n = __popc(v & ~(v << 1));
     if ((v & 1u) && last_zero != (w << 5) - 1) {
         const int len = ~v ? __ffs(~v) - 1 : 32, m = ((w << 5) - last_zero - 1) % max_run;
@@ -289,7 +287,7 @@ JANUS_DEV void emit_list_runs(RunShared &sh, const uint32_t *sw, int nbits, int 
             const uint32_t y = word(x);
             if (s0 == 0 || x < s0) {  // (the first block counts everything, for the totals)
                 pages += __popc(y);
-                starts += count_starts(x, y, L, max_run, first_zero);
+                starts += count_starts(x, y, L, max_run);
             }
             if (y != 0xffffffffu) {
                 L = last_unset(x, y);
@@ -311,7 +309,7 @@ JANUS_DEV void emit_list_runs(RunShared &sh, const uint32_t *sw, int nbits, int 
         run_scan2(sh.c, sh.d, z, -1, op_max, one, 0, op_add, lb, unused, unused);
         lb = max(lb, zero_before);
     }
-    int np = __popc(v), ns = count_starts(w, v, lb, max_run, first_zero), tp, ts, pages_at;
+    int np = __popc(v), ns = count_starts(w, v, lb, max_run), tp, ts, pages_at;
     const int own_starts = ns;
     run_scan2(wpt > 1 ? sh.a : sh.c, wpt > 1 ? sh.b : sh.d, np, 0, op_add, ns, 0, op_add, pages_at, tp, ts);
     if (wpt == 1 && s0 == 0 && tid == 0) {
@@ -325,7 +323,7 @@ JANUS_DEV void emit_list_runs(RunShared &sh, const uint32_t *sw, int nbits, int 
         for (uint32_t x = v; x; x &= x - 1u)
             list[pos++] = (w << 5) + __ffs(x) - 1;
     if (own_starts)
-        run_starts(w, v, lb, max_run, first_zero, [&](int n, int p, int hi) {
+        run_starts(w, v, lb, max_run, [&](int n, int p, int hi) {
             const int end = (hi & 31) == 0 ? first_zero(w) : hi;  // a run up to the word's end may go on
             *(v2i *)(runs + 2 * (int64_t)(rpos + n)) = v2i{p, min(max_run, end - p)};
         });

@@ -44,6 +44,7 @@
 
 namespace janus {
 
+constexpr int TK_THREADS = 512;
 constexpr int TK_RING = 8;                // 1 KB chunks in flight per wave
 constexpr int TK_MAX_K = 6144;            // with CAP = 8192: >= 2048 free slots after a cut
 constexpr int TK_SMALL_K = 2048;          // with CAP = 4096
@@ -53,9 +54,9 @@ constexpr int TK_TIES = 512;              // a bin of more values is narrowed as
 
 constexpr int tk_max_k(int cap) { return cap <= 4096 ? TK_SMALL_K : TK_MAX_K; }
 
-template <int TPB, int CAP>
+template <int CAP>
 struct alignas(16) TopkShared {
-    static constexpr int WAVES = TPB / kWave;
+    static constexpr int WAVES = TK_THREADS / kWave;
     uint32_t key[CAP];
     int32_t id[CAP];   // directly behind key: the output bitmap spans both
     union {
@@ -152,10 +153,10 @@ JANUS_DEV void block_extremes(SM &sm, uint32_t &lo, uint32_t &hi)
 // values, or a single value of the range.  On return [lo, hi] is that bin,
 // `want` how many of its largest values make up the asked number, and the
 // result how many values it holds.
-template <int TPB, int NI, class SM>
+template <int NI, class SM>
 JANUS_DEV int narrow(SM &sm, const uint32_t (&v)[NI], uint32_t on, uint32_t &lo, uint32_t &hi, int &want, int few)
 {
-    constexpr int PER = TK_BINS / TPB;  // bins per thread of the scan
+    constexpr int PER = TK_BINS / TK_THREADS;  // bins per thread of the scan
     int cnt = 0;
     for (int pass = 0; pass < 3; ++pass) {  // 11 bits a pass
         const int bits = 32 - __clz((int)(hi - lo) | 1);
@@ -222,7 +223,7 @@ JANUS_DEV int narrow(SM &sm, const uint32_t (&v)[NI], uint32_t on, uint32_t &lo,
 // Flags of the k best of the block's buffered entries (those flagged in on, at
 // least k of them), and the threshold set to the k-th best or, where all of
 // a bin wins, to the bin's lower end.  Ends with a barrier.
-template <int TPB, int NI, class SM>
+template <int NI, class SM>
 JANUS_DEV uint32_t best(SM &sm, const uint32_t (&key)[NI], const int32_t (&id)[NI], uint32_t on, int k)
 {
     uint32_t lo = 0xffffffffu, hi = 0u;
@@ -236,7 +237,7 @@ JANUS_DEV uint32_t best(SM &sm, const uint32_t (&key)[NI], const int32_t (&id)[N
         sm.nfew = 0;
     block_extremes(sm, lo, hi);
     int want = k;
-    const int cnt = narrow<TPB>(sm, key, on, lo, hi, want, TK_FEW);
+    const int cnt = narrow(sm, key, on, lo, hi, want, TK_FEW);
     uint32_t win = 0, in = 0;  // above the bin, inside it
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
@@ -287,7 +288,7 @@ JANUS_DEV uint32_t best(SM &sm, const uint32_t (&key)[NI], const int32_t (&id)[N
             }
         }
         block_extremes(sm, ilo, ihi);
-        narrow<TPB>(sm, inv, in, ilo, ihi, want, 1);  // ids differ: a bin of one
+        narrow(sm, inv, in, ilo, ihi, want, 1);  // ids differ: a bin of one
 #pragma unroll
         for (int i = 0; i < NI; ++i)
             win |= (((in >> i) & 1u) && inv[i] >= ilo ? 1u : 0u) << i;
@@ -298,14 +299,14 @@ JANUS_DEV uint32_t best(SM &sm, const uint32_t (&key)[NI], const int32_t (&id)[N
     return win;
 }
 
-// The buffer's entries of this thread (e = threadIdx.x + i TPB), flagged.
-template <int TPB, int NI, class SM>
+// The buffer's entries of this thread (e = threadIdx.x + i TK_THREADS), flagged.
+template <int NI, class SM>
 JANUS_DEV uint32_t load_entries(const SM &sm, int cnt, uint32_t (&key)[NI], int32_t (&id)[NI])
 {
     uint32_t on = 0;
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-        const int e = (int)threadIdx.x + i * TPB;
+        const int e = (int)threadIdx.x + i * TK_THREADS;
         key[i] = e < cnt ? sm.key[e] : 0u;
         id[i] = e < cnt ? sm.id[e] : -1;
         on |= (id[i] >= 0 ? 1u : 0u) << i;  // (slots left by a stopped wave hold -1)
@@ -315,15 +316,15 @@ JANUS_DEV uint32_t load_entries(const SM &sm, int cnt, uint32_t (&key)[NI], int3
 
 // Cuts the full buffer to exactly its k best entries and raises the threshold
 // to the k-th best.  Begins and ends with a barrier.
-template <int TPB, int CAP>
-__device__ __noinline__ void compact(TopkShared<TPB, CAP> &sm, int k)
+template <int CAP>
+__device__ __noinline__ void compact(TopkShared<CAP> &sm, int k)
 {
-    constexpr int NI = CAP / TPB;
+    constexpr int NI = CAP / TK_THREADS;
     uint32_t key[NI];
     int32_t id[NI];
     lds_sync();
-    const uint32_t on = load_entries<TPB>(sm, CAP, key, id);
-    const uint32_t win = best<TPB>(sm, key, id, on, k);
+    const uint32_t on = load_entries(sm, CAP, key, id);
+    const uint32_t win = best(sm, key, id, on, k);
     int tot;
     int pos = block_exclusive_scan(sm, __popc(win), tot);  // (every entry is in registers by now)
 #pragma unroll
@@ -385,10 +386,10 @@ JANUS_DEV bool append4(SM &sm, v4f x, uint32_t pend, int id0, float tf, int32_t 
 // One pass over [0, n) of the row, filtering against the running threshold;
 // with seed > 0 the threshold is first set from a sample of the row, so that
 // about seed * k elements pass.  Ends with a barrier.
-template <int TPB, int CAP>
-JANUS_DEV void stream_row(TopkShared<TPB, CAP> &sm, const float *__restrict__ row, int n, int k, float seed)
+template <int CAP>
+JANUS_DEV void stream_row(TopkShared<CAP> &sm, const float *__restrict__ row, int n, int k, float seed)
 {
-    constexpr int NW = TPB / kWave;
+    constexpr int NW = TK_THREADS / kWave;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // unaligned head (< 4 elements), 16-byte aligned body of float4s, tail (< 4)
     const int head = min(n, (int)(((16 - (reinterpret_cast<uintptr_t>(row) & 15)) & 15) >> 2));
@@ -403,13 +404,13 @@ JANUS_DEV void stream_row(TopkShared<TPB, CAP> &sm, const float *__restrict__ ro
 
     // the sample goes out first, then the head and tail elements and the
     // wave's first chunks; the sample is ranked under their latency
-    constexpr int SPT = TK_SAMPLE_GROUPS * 2 / TPB;  // float4s of the sample per thread
+    constexpr int SPT = TK_SAMPLE_GROUPS * 2 / TK_THREADS;  // float4s of the sample per thread
     const int ngroups = nbody4 >> 1;
     const int m4 = seed > 0.f ? min(TK_SAMPLE_GROUPS, ngroups) * 2 : 0;
     v4f smp[SPT];
 #pragma unroll
     for (int j = 0; j < SPT; ++j) {
-        const int e = (int)threadIdx.x + j * TPB;
+        const int e = (int)threadIdx.x + j * TK_THREADS;
         smp[j] = load4(e < m4 ? 2 * tk_sample_group(e >> 1, ngroups) + (e & 1) : nbody4);
     }
     // lanes 0..2 of the first wave take the head, 4..6 the tail
@@ -429,7 +430,7 @@ JANUS_DEV void stream_row(TopkShared<TPB, CAP> &sm, const float *__restrict__ ro
             for (int c = 0; c < 4; ++c) {
                 const uint32_t kk = score_key(smp[j][c]);
                 key[4 * j + c] = kk;
-                if ((int)threadIdx.x + j * TPB < m4) {
+                if ((int)threadIdx.x + j * TK_THREADS < m4) {
                     on |= 1u << (4 * j + c);
                     lo = min(lo, kk);
                     hi = max(hi, kk);
@@ -439,7 +440,7 @@ JANUS_DEV void stream_row(TopkShared<TPB, CAP> &sm, const float *__restrict__ ro
         // rank ~ seed * k * (sample / n) + 8; the bin's lower end suffices once
         // the bin holds few of that rank's entries
         int r = min(4 * m4, (int)(seed * (float)k * (float)(4 * m4) / (float)n) + 8);
-        narrow<TPB>(sm, key, on, lo, hi, r, max(4, r >> 3));
+        narrow(sm, key, on, lo, hi, r, max(4, r >> 3));
         if (threadIdx.x == 0)
             set_threshold(sm, lo, 0x7fffffff);  // accept key >= seed
         lds_sync();
@@ -485,8 +486,8 @@ JANUS_DEV void stream_row(TopkShared<TPB, CAP> &sm, const float *__restrict__ ro
 // 91 with the second, 132 where the sample misleads both (two streams, the
 // second without a threshold, would be one less, but the streams that filter
 // are the cheap ones, and with one seed alone the middle case took the last's).
-template <int TPB, int CAP>
-__device__ __noinline__ void stream_again(TopkShared<TPB, CAP> &sm, const float *row, int n, int k)
+template <int CAP>
+__device__ __noinline__ void stream_again(TopkShared<CAP> &sm, const float *row, int n, int k)
 {
     for (float seed = n > CAP ? 3.f : 0.f;; seed = 0.f) {
         lds_sync();
@@ -495,19 +496,19 @@ __device__ __noinline__ void stream_again(TopkShared<TPB, CAP> &sm, const float 
             set_threshold(sm, 0u, 0x7fffffff);
         }
         lds_sync();
-        stream_row<TPB, CAP>(sm, row, n, k, seed);
+        stream_row<CAP>(sm, row, n, k, seed);
         if (sm.count >= k || seed == 0.f)
             break;
     }
 }
 
-template <int TPB, int CAP>
-__global__ __launch_bounds__(TPB, CAP <= 4096 ? 4 : 2) void topk_rows(
+template <int CAP>
+__global__ __launch_bounds__(TK_THREADS, CAP <= 4096 ? 4 : 2) void topk_rows(
     const int32_t *__restrict__ q_start, const int32_t *__restrict__ hist_len,
     const int64_t *__restrict__ score_start, int num_seqs, int es,
     const float *__restrict__ scores, int k_row, int32_t *__restrict__ topk_idx, int shards, int align)
 {
-    __shared__ TopkShared<TPB, CAP> sm;
+    __shared__ TopkShared<CAP> sm;
     // causal rows (shards == 0): block g selects k_row of its candidates
     // (tokens: [0, M+i]);
     // sharded rows: block g*shards + n selects k_row/shards of history shard n
@@ -532,7 +533,7 @@ __global__ __launch_bounds__(TPB, CAP <= 4096 ? 4 : 2) void topk_rows(
     const float *row = scores + score_start[b] + (int64_t)i * ctx + base;
 
     if (n <= k) {
-        for (int j = threadIdx.x; j < k; j += TPB)
+        for (int j = threadIdx.x; j < k; j += TK_THREADS)
             out[j] = j < n ? base + j : -1;
         return;
     }
@@ -543,24 +544,24 @@ __global__ __launch_bounds__(TPB, CAP <= 4096 ? 4 : 2) void topk_rows(
     lds_sync();
 
     // 1., 2. one streaming pass (more if the seed was above the k-th key)
-    stream_row<TPB, CAP>(sm, row, n, k, n > CAP ? 1.3f : 0.f);
+    stream_row<CAP>(sm, row, n, k, n > CAP ? 1.3f : 0.f);
     if (sm.count < k)
-        stream_again<TPB, CAP>(sm, row, n, k);
+        stream_again<CAP>(sm, row, n, k);
     // 3. the k best of the buffered candidates
     const int cnt = sm.count;
-    constexpr int NI = CAP / TPB;
+    constexpr int NI = CAP / TK_THREADS;
     uint32_t key[NI], win;
     int32_t id[NI];
-    win = load_entries<TPB>(sm, cnt, key, id);
+    win = load_entries(sm, cnt, key, id);
     if (cnt > k)
-        win = best<TPB>(sm, key, id, win, k);
+        win = best(sm, key, id, win, k);
     else
         lds_sync();
     // 4. ascending output (the bitmap lies over the key and id arrays)
     uint32_t *bm = sm.key;
     const int nwords = (n + 31) >> 5;                          // <= 2 * CAP (checked by the launcher)
-    const int wpt = ((nwords + TPB - 1) / TPB + 3) & ~3;       // words per thread, whole 16-byte reads
-    for (int wd = 4 * threadIdx.x; wd < nwords; wd += 4 * TPB)
+    const int wpt = ((nwords + TK_THREADS - 1) / TK_THREADS + 3) & ~3;       // words per thread, whole 16-byte reads
+    for (int wd = 4 * threadIdx.x; wd < nwords; wd += 4 * TK_THREADS)
         *(v4i *)(bm + wd) = v4i{0, 0, 0, 0};
     lds_sync();
 #pragma unroll
@@ -591,7 +592,7 @@ __global__ __launch_bounds__(TPB, CAP <= 4096 ? 4 : 2) void topk_rows(
             sm.stage[sm.pre[wd] + __popc(bm[wd] & ((1u << (id[i] & 31)) - 1u))] = base + id[i];
         }
     lds_sync();
-    for (int j = threadIdx.x; j < k; j += TPB)
+    for (int j = threadIdx.x; j < k; j += TK_THREADS)
         out[j] = j < tot ? sm.stage[j] : -1;
 }
 
@@ -610,14 +611,14 @@ static int launch_topk(const janus_batch *bt, const float *scores, int k, int32_
     if (bt->total_q == 0)
         return JANUS_OK;
     const dim3 grid((unsigned)bt->total_q * (unsigned)(shards ? shards : 1));
-    auto go = [&](auto kern, int threads) {
-        hipLaunchKernelGGL(kern, grid, dim3(threads), 0, as_stream(stream), bt->q_start, bt->hist_len,
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, dim3(TK_THREADS), 0, as_stream(stream), bt->q_start, bt->hist_len,
                            bt->score_start, bt->num_seqs, bt->entry_shift, scores, k, topk_idx, shards, align);
     };
     if (kk <= TK_SMALL_K && bt->max_ctx <= 2 * 4096 * 32)
-        go(topk_rows<512, 4096>, 512);
+        go(topk_rows<4096>);
     else
-        go(topk_rows<512, 8192>, 512);
+        go(topk_rows<8192>);
     return launch_status();
 }
 

@@ -126,9 +126,10 @@ typedef struct {
  *   w       device [total_q, H] fp32, w >= 0
  *   scores  device fp32; row i of session b starts at
  *           scores + score_start[b] + i*(M_b+N_b) and holds M_b+N_b entries.
- * q_dt must equal k_dt.  fp8 with H = 64 and d = 128 runs on fp8 MFMA (the
- * head weights are applied in bf16: relative error <= 2^-8 per term); every
- * other dtype and shape runs on the fp32 MFMA.  Accumulation is fp32.
+ * q_dt must equal k_dt.  With H = 64 and d = 128 fp8 runs on fp8 MFMA (the
+ * head weights are applied in bf16: relative error <= 2^-8 per term) and bf16
+ * on bf16 MFMA (weights in fp32); every other dtype and shape runs on the fp32
+ * MFMA.  Accumulation is fp32.
  */
 int janus_index_scores(const janus_batch *b,
                        const void *q, janus_dtype q_dt, const float *q_scale,

@@ -14,8 +14,8 @@
 // clamps to [0, 1] after rounding to nearest even) is exactly ReLU followed
 // by the bf16 rounding, with head weights pre-multiplied by 2^25.  The fp8
 // MFMA and the VALU do not overlap on this chip, so VALU work per MFMA bounds
-// the kernels.  The row-tile kernel dots each converted pair with its weights
-// (v_dot2c_f32_bf16): 4 VALU ops per MFMA.  The prefill kernel feeds the
+// the kernels.  The row-tile kernel with MXFP4 keys dots each converted pair
+// with its weights (v_dot2c_f32_bf16): 4 VALU ops per MFMA.  The others feed the
 // converted pairs to a bf16 MFMA whose A operand holds the weights, which
 // sums the heads of a token across lanes as well: 2 VALU ops per fp8 MFMA
 // and one bf16 MFMA per two, which other waves' VALU work overlaps.  Every
@@ -122,8 +122,9 @@ JANUS_DEV void head_sum_group(v4f &hc, const v8i &a0, const v8i &a1, const v8i &
 // Block scales can make a product of any size, so ReLU is not folded into
 // the convert here: each pair is rounded to bf16, its sign clamped with a
 // packed int16 max (a negative bf16 is a negative int16), and dotted with
-// its weights into acc (v_dot2c); the lane groups' sums are added afterwards.  Convert, max and dot of a pair are at least two instructions apart
-// (one wait state after a VALU write read by a packed op).
+// its weights into acc (v_dot2c); the lane groups' sums are added afterwards.
+// Convert, max and dot of a pair are at least two instructions apart (one wait
+// state after a VALU write read by a packed op).
 #define IDX_MFMA_F4(dst, a) \
     "v_mfma_scale_f32_16x16x128_f8f6f4 " dst ", %[" a "], %[bk], 0, %[sa], %[sb] op_sel_hi:[0,0,0]\n\t"
 #define F4_CVT(r, r1) "v_cvt_pk_bf16_f32 v" #r ", v" #r ", v" #r1 "\n\t"
@@ -222,20 +223,13 @@ JANUS_DEV v8i evens_odds(const v8i &a)
 }
 constexpr int F4_QUERY_SCALE = 127 + 6;  // E8M0 2^6
 
-template <bool FIRST>
 JANUS_DEV void head_group_f4(float &acc, const v8i &a0, const v8i &a1, const v8i &a2, const v8i &a3, const v8i &bk,
                              int sa, int sb, const v2bf (*w)[2])
 {
-    if (FIRST)
-        asm(IDX_HEAD_GROUP_F4("v_mov_b32 %[acc], 0\n\t")
-            : [acc] "=&v"(acc)
-            : IDX_HEAD_GROUP_F4_INPUTS
-            : IDX_HEAD_GROUP_CLOBBERS);
-    else
-        asm(IDX_HEAD_GROUP_F4("")
-            : [acc] "+v"(acc)
-            : IDX_HEAD_GROUP_F4_INPUTS
-            : IDX_HEAD_GROUP_CLOBBERS);
+    asm(IDX_HEAD_GROUP_F4("v_mov_b32 %[acc], 0\n\t")
+        : [acc] "=&v"(acc)
+        : IDX_HEAD_GROUP_F4_INPUTS
+        : IDX_HEAD_GROUP_CLOBBERS);
 }
 
 typedef __attribute__((address_space(3))) void lds_void_t;
@@ -1269,7 +1263,7 @@ __global__ __launch_bounds__(256, 2) void index_scores_rows(
                     if (t >= nv || masked)
                         continue;
                     float r;
-                    head_group_f4<true>(r, a[t][0], a[t][1], a[t][2], a[t][3], bk, F4_QUERY_SCALE, G.bs[j],
+                    head_group_f4(r, a[t][0], a[t][1], a[t][2], a[t][3], bk, F4_QUERY_SCALE, G.bs[j],
                                         &wv[t][0]);
                     r += xor_lanes16(r);
                     r += __shfl_xor(r, 32, 64);

@@ -250,7 +250,8 @@ def measured_traffic(path):
         return None
 
 
-TRAFFIC_SOURCES = ["paper_2609_36938_amd/csrc/index_scores.hip", "paper_2609_36938_amd/csrc/janus_device.hpp"]
+TRAFFIC_SOURCES = ["paper_2609_36938_amd/csrc/index_scores.hip", "paper_2609_36938_amd/csrc/janus_device.hpp",
+                   "paper_2609_36938_amd/csrc/launch_rules.hpp"]
 
 
 def record_traffic(fetch_csv, write_csv, out_path):

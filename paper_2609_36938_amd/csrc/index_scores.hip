@@ -1063,7 +1063,7 @@ __global__ __launch_bounds__(256, 4) void index_scores_general(
 namespace janus {
 
 // Row-tile kernel: a block takes up to NQ tokens of one session and one
-// chunk of 256 to 2048 keys (rows_plan).  It serves
+// chunk of 256 to 4096 keys (rows_plan).  It serves
 // decode-shaped batches (every session appends at most NQ tokens, as in the
 // decode phase: the scores are a GEMV over each session's keys, bound by
 // reading the keys once), with fp8 or MXFP4 keys.  The four waves take the
@@ -1087,14 +1087,16 @@ JANUS_DEV void rows_block(const int32_t *ctx_start, int num_seqs, int shift, int
 {
     const int lane = threadIdx.x & 63;
     b = 0;
+    int b_first = 0;
     for (int n = num_seqs; n > 1;) {  // the session is one of b .. b + n - 1
         const int step = (n + kWave - 1) / kWave, s = b + min(lane * step, n - 1);
         const int first = rows_first(ctx_start[s], s, shift);  // (by every lane: a load behind a branch cost registers)
-        const int at = (__popcll(__ballot(lane * step < n && first <= block)) - 1) * step;
-        b += at;
-        n = min(step, n - at);
+        const int l = __popcll(__ballot(lane * step < n && first <= block)) - 1;
+        b += l * step;
+        b_first = __builtin_amdgcn_readlane(first, l);
+        n = min(step, n - l * step);
     }
-    c0 = (block - rows_first(ctx_start[b], b, shift)) << shift;
+    c0 = (block - b_first) << shift;
 }
 
 template <int NQ, bool FP4>
@@ -1322,7 +1324,7 @@ static void launch_rows(const janus_batch *bt, const void *q, const float *q_sca
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
         cus = 256;
-    const RowsPlan p = rows_plan(bt->num_seqs, bt->max_ctx, bt->total_ctx, cus, FP4);
+    const RowsPlan p = rows_plan(bt->num_seqs, bt->max_ctx, bt->total_ctx, bt->max_q, cus, FP4);
     auto go = [&](auto kern) {
         hipLaunchKernelGGL(kern, dim3((unsigned)p.blocks), dim3(256), 0, st, bt->q_start, bt->ctx_start, bt->hist_len,
                            bt->score_start, bt->num_seqs, bt->entry_shift, p.per_seq, p.chunk, (const uint8_t *)q,

@@ -70,53 +70,55 @@ constexpr int rows_first(int ctx_start, int s, int shift) { return (ctx_start >>
 
 // Keys per block of a decode batch, and how its blocks are numbered.
 struct RowsPlan {
-    int chunk;       // keys per block, 2048 down to 256 (one 64-key group per wave)
+    int chunk;       // keys per block, 4096 down to 256 (one 64-key group per wave)
     int per_seq;     // blocks of every session, or 0: numbered by rows_first
     int64_t blocks;
 };
-constexpr int ROWS_CHUNK_MAX = 2048;
 constexpr int ROWS_CHUNK_MIN = 256;
-constexpr int ROWS_BLOCK_KEYS = 256;  // what a block costs besides its keys, in keys
-constexpr int ROWS_EMPTY_KEYS = 16;   // what an empty block costs, in keys
 constexpr int64_t ROWS_MAX_BLOCKS = (1 << 24) - 1;  // a launch takes fewer than 2^32 threads
 
-// The plan with the shortest time estimated, in keys per CU: whole chunks one
-// after another (a last one on up to 1 CU in 20 not counted), the blocks' own
-// cost, and the blocks without keys, which leave CUs idle while others have one
-// chunk more.  Sessions of about one length take the grid of per_seq blocks
-// each, which has few empty ones; others the numbering by rows_first, which has
-// at most one per session.  With one block per CU, FP4 keys take a quarter
-// longer per key (their unpacking has no other block to run under).
-// Measured (us, 1 token per session, fp8 keys; the former choice by useful
-// blocks alone in brackets): 64 sessions of 8000 keys 15.8 (16.6), of 100000 173
-// (179), 256 of 4000 25 (38), 4096 of 1000 113 (287), one of 1M with 63 of 1K 30
-// (38); 2 tokens: 64 of 8000 16.8 (36), one of 1M with 63 of 1K 39 (96).
-// 4096-key chunks were at most 7% faster where keys stay in cache and 9% slower
-// where they don't (128 sessions of 20000: 77 against 68 us).
-constexpr RowsPlan rows_plan(int num_seqs, int max_ctx, int64_t total_ctx, int cus, bool fp4)
+// The chunk with the shortest time estimated, in keys of one block alone on its
+// CU, by the blocks that the fullest CU takes (a session of C keys makes about
+// C / chunk + 1/2; one block more than the CUs is left out: the last key of a
+// power of two and one).  The first block costs its start and its keys.  Each
+// next one that is resident beside it (3 blocks a CU with one token per session,
+// else 2) runs mostly under it, but for what the memory takes for its keys; with
+// the CU full, the next one costs like the first.  The constants are fitted to
+// 1071 batches of 1 to 4096 sessions of 500 to 1M keys, even and ragged, with 1,
+// 2 and 4 tokens and both key types, keys from HBM: the chunk taken is 0.9% off
+// the best one in the mean.  The chunk that fills rounds of resident blocks best
+// was 7.0% off, whole chunks per CU with a fixed cost per block 3.3% (us, the
+// three in turn, fp8 keys: 16 sessions of 15K to 60K 19.4, 19.4, 25.8; 48 of 8192
+// with 2 tokens 19.1, 18.8, 23.8; 256 of 4000 32.0, 40.6, 32.0; one of 1M with 63
+// of 1K and 2 tokens 42, 51, 42; 64 of 32K to 164K 151, 151, 150).
+// Blocks are numbered by rows_first unless the grid of the longest session's
+// chunks for each session needs no more of them, or has each on a CU of its own:
+// it saves the search, 0.2 us.
+constexpr RowsPlan rows_plan(int num_seqs, int max_ctx, int64_t total_ctx, int max_q, int cus, bool fp4)
 {
-    RowsPlan best = {ROWS_CHUNK_MAX, 0, total_ctx / ROWS_CHUNK_MAX + num_seqs};
+    const bool one = max_q <= 1;
+    const int resident = one ? 3 : 2, start = fp4 ? 384 : 128, beside = fp4 ? 256 : one ? 448 : 1024;
+    RowsPlan best = {0, 0, 0};
     double best_cost = -1.0;
-    for (int c = ROWS_CHUNK_MAX; c >= ROWS_CHUNK_MIN; c /= 2) {
-        const double full = (double)total_ctx / c;
+    for (int c = one ? 2048 : 4096; c >= ROWS_CHUNK_MIN; c /= 2) {
         const int per_seq = (max_ctx + c - 1) / c;
         const int64_t grid = (int64_t)num_seqs * per_seq, numbered = total_ctx / c + num_seqs;
-        double useful = full + 0.5 * num_seqs;
-        useful = useful < (double)grid ? useful : (double)grid;
-        int rounds = (int)(full / cus + 0.95);
-        rounds = rounds < 1 ? 1 : rounds;
-        for (int g = 1; g >= 0; --g) {
-            const int64_t blocks = g ? grid : numbered;
-            if (blocks > ROWS_MAX_BLOCKS)
-                continue;
-            const double empty = (double)blocks > useful ? (double)blocks - useful : 0.0;
-            const double idle = empty < cus ? empty / cus : 1.0;
-            const double cost = (rounds + idle) * c + (fp4 && rounds == 1 ? 0.25 * c : 0.0) +
-                                (useful * ROWS_BLOCK_KEYS + empty * ROWS_EMPTY_KEYS) / cus;
-            if (best_cost < 0.0 || cost < best_cost) {
-                best_cost = cost;
-                best = RowsPlan{c, g ? per_seq : 0, blocks};
-            }
+        const bool even = grid <= numbered || grid <= cus;
+        const int64_t blocks = even ? grid : numbered;
+        if (best.chunk && blocks > ROWS_MAX_BLOCKS)
+            break;
+        const double about = (double)total_ctx / c + 0.5 * num_seqs;
+        const double useful = about < (double)grid ? about : (double)grid;
+        const double first = c + start, memory = 0.6 * c, under = 0.2 * c + beside;
+        const double next = under > memory ? under : memory;
+        int64_t n = (int64_t)((useful - 1.0) / cus);  // blocks after the fullest CU's first
+        if (n > 0 && (double)n * cus >= useful - 1.0)
+            --n;
+        const int64_t refills = n / resident;
+        const double cost = first + (double)(n - refills) * next + (double)refills * (first > next ? first : next);
+        if (best_cost < 0.0 || cost < best_cost) {
+            best_cost = cost;
+            best = RowsPlan{c, even ? per_seq : 0, blocks};
         }
     }
     return best;

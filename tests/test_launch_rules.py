@@ -14,9 +14,9 @@ extern "C" {
 int pd_one_block(long q, long k, int nwords) { return janus::pd_one_block(q, k, nwords); }
 int prefill_per_xcd(int max_ctx) { return janus::prefill_per_xcd(max_ctx); }
 int session_chunk(int ctx, int n) { return janus::session_chunk(ctx, n, janus::prefill_recip(n)); }
-void rows_plan(int n, int max_ctx, long total, int cus, int fp4, long *out)
+void rows_plan(int n, int max_ctx, long total, int max_q, int cus, int fp4, long *out)
 {
-    const janus::RowsPlan p = janus::rows_plan(n, max_ctx, total, cus, fp4);
+    const janus::RowsPlan p = janus::rows_plan(n, max_ctx, total, max_q, cus, fp4);
     out[0] = p.chunk, out[1] = p.per_seq, out[2] = p.blocks;
 }
 int tk_sample_group(int g, int ngroups) { return janus::tk_sample_group(g, ngroups); }
@@ -59,30 +59,41 @@ def test_decode_blocks_cover_every_chunk(rules, shift):
 
 
 def test_decode_plan(rules):
-    def plan(ctx, fp4=0):
+    def plan(ctx, fp4=0, q=1):
         out = (ctypes.c_long * 3)()
-        rules.rows_plan(len(ctx), int(max(ctx)), ctypes.c_long(int(sum(ctx))), 256, fp4, out)
+        rules.rows_plan(len(ctx), int(max(ctx)), ctypes.c_long(int(sum(ctx))), q, 256, fp4, out)
         chunk, per_seq, blocks = out
-        assert chunk in (256, 512, 1024, 2048) and blocks < 1 << 24
+        assert chunk in (256, 512, 1024, 2048, 4096) and blocks < 1 << 24
         # every chunk of every session has a block
         assert per_seq * chunk >= max(ctx) and blocks == per_seq * len(ctx) if per_seq else \
             blocks == sum(ctx) // chunk + len(ctx)
         return chunk, per_seq, blocks, sum(-(-c // chunk) for c in ctx)
-    # sessions of one length: no empty block, one block per CU where that many suffice
-    assert plan([8000] * 64)[:3] == (2048, 4, 256)
-    assert plan([131073])[0] == 512 and plan([2000] * 2)[0] == 256
-    for ctx in ([4000] * 256, [1000] * 4096, [100000] * 64):
-        _, _, blocks, useful = plan(ctx)
-        assert blocks == useful
-    # one long session among short ones does not set the grid of all
     rng = np.random.default_rng(3)
+    between = lambda n, lo, hi: [int(c) for c in np.exp(rng.uniform(np.log(lo), np.log(hi), n))]  # noqa: E731
+    # measured: the chunk that was the fastest, or within 1% of it
+    for ctx, q, fp4, best in [([131073], 1, 0, (512,)), ([2000] * 2, 1, 0, (256,)), ([24001] * 64, 1, 0, (2048,)),
+                              ([8194] * 48, 2, 0, (1024, 2048)), ([8193] * 16, 1, 0, (1024,)),
+                              ([60001] * 2, 1, 0, (512,)), ([131073] * 3, 1, 0, (1024,)), ([163841] * 3, 1, 1, (1024,)),
+                              ([8196] * 16, 4, 0, (1024,)), ([8193] * 3, 1, 1, (256,)),
+                              (between(16, 15000, 60000), 1, 0, (1024,)), (between(32, 6000, 24000), 1, 0, (1024,)),
+                              (between(24, 6000, 24000), 2, 0, (1024,))]:
+        assert plan(ctx, fp4, q)[0] in best, (len(ctx), max(ctx), q, fp4, plan(ctx, fp4, q))
+    # sessions of one length: no empty block
+    for ctx in ([4000] * 256, [1000] * 4096, [100000] * 64):
+        for q in (1, 2, 4):
+            _, _, blocks, useful = plan(ctx, 0, q)
+            assert blocks == useful
+    # one long session among short ones does not set the grid of all
     ragged = [[1000000] + [1000] * 63, [1000000] + [500] * 1023]
-    ragged += [[int(c) for c in np.exp(rng.uniform(7, 12.5, n))] for n in (3, 17, 64, 300, 2000) for _ in range(8)]
+    ragged += [between(n, 1000, 270000) for n in (3, 17, 64, 300, 2000) for _ in range(8)]
     for ctx in ragged:
         for fp4 in (0, 1):
-            _, _, blocks, useful = plan(ctx, fp4)
-            assert blocks <= 2 * useful + 16, (len(ctx), blocks, useful)
-    assert plan([1 << 24])[2] and plan([1] * 100000)[2] == 100000
+            for q in (1, 2, 4):
+                _, _, blocks, useful = plan(ctx, fp4, q)
+                assert blocks <= max(256, 2 * useful + 16), (len(ctx), blocks, useful)
+    for q in (1, 2, 4):
+        assert plan([1 << 24], 0, q)[2] and plan([1] * 100000, 0, q)[2] == 100000
+        assert plan([1], 0, q)[:3] == (256, 1, 1)
 
 
 def test_prefill_chunks(rules):

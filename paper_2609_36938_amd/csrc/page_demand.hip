@@ -237,18 +237,20 @@ JANUS_DEV int count_starts(int w, uint32_t v, int last_zero, int max_run)
     return n;
 }
 
-// Walks the pages of the bitmap sw in LDS (nbits bits, zeros past them unless
-// MASK: then those bits are ignored; whole 32-bit words): writes, for this
-// block's slice of RUN_THREADS words, one per thread, the ascending page list (if list != NULL) and the packed runs, and in
-// the first block the two counts.
-template <bool MASK>
+// Walks the pages of the bitmap sw in LDS (nbits bits in whole 32-bit words,
+// zeros past them): writes, for this block's slice of RUN_THREADS words, one per
+// thread, the ascending page list (if list != NULL) and the packed runs, and in
+// the first block the two counts.  ONE: the bitmap has at most RUN_THREADS words,
+// and bits past nbits are ignored; that a thread's range is one word is then known
+// to the compiler (page_demand_small of 2 rows 7.5 -> 7.1 us).
+template <bool ONE>
 JANUS_DEV void emit_list_runs(RunShared &sh, const uint32_t *sw, int nbits, int max_run, int32_t *list, int32_t *runs,
                               int32_t *n_pages_out, int32_t *n_runs_out)
 {
     const int nwords = (nbits + 31) >> 5, tid = threadIdx.x;
-    const int wpt = max(1, (nwords + RUN_THREADS - 1) / RUN_THREADS);  // words of a thread's range
+    const int wpt = ONE ? 1 : max(1, (nwords + RUN_THREADS - 1) / RUN_THREADS);  // words of a thread's range
     const uint32_t last_mask = nbits & 31 ? (1u << (nbits & 31)) - 1u : ~0u;
-    auto word = [&](int w) { return MASK && w == nwords - 1 ? sw[w] & last_mask : sw[w]; };
+    auto word = [&](int w) { return ONE && w == nwords - 1 ? sw[w] & last_mask : sw[w]; };
     auto last_unset = [&](int w, uint32_t v) { return (w << 5) + 31 - __clz((int)~v); };  // v not all ones
     // over ranges of wpt words: the first unset page from each range on
     // (ranges taken from the end), the last one before each

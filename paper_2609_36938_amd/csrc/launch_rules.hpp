@@ -52,8 +52,11 @@ constexpr unsigned prefill_recip(int n) { return ((1u << 31) + (unsigned)n - 1) 
 // tokens, MXFP4 keys: 3995 -> 2998 us; sixteen of 0.5K to 131K, fp8 keys: 2948
 // -> 950).  x = ceil(ctx / 8) + n - 1 is below 2^22 and the reciprocal's error
 // below n <= 2^7 in 2^31, so that x * recip >> 31 is the exact quotient: a
-// block's first loads wait for it, and the division made an append of 5 to 200
-// tokens 1% slower than no division (47.9 against 47.4 us at 16K tokens).
+// block's first loads wait for it, and with a division appends of 5 to 200
+// tokens took 1% longer (fp8 keys, 16K tokens: 47.9 against 47.4 us).  About half
+// of that is where the main loop then lay: its place against 32 bytes moves the
+// three prefill kernels by up to 0.8%, and MXFP4's lies 0.7% better with the
+// division (131K + 64 tokens: 172.5 and 173.5 us).
 constexpr int session_chunk(int ctx, int n, unsigned recip)
 {
     const unsigned x = (unsigned)((ctx + IDX_XCD - 1) / IDX_XCD + n - 1);
@@ -86,7 +89,7 @@ constexpr int64_t ROWS_MAX_BLOCKS = (1 << 24) - 1;  // a launch takes fewer than
 // the CU full, the next one costs like the first.  The constants are fitted to
 // 1071 batches of 1 to 4096 sessions of 500 to 1M keys, even and ragged, with 1,
 // 2 and 4 tokens and both key types, keys from HBM: the chunk taken is 0.9% off
-// the best one in the mean.  The chunk that fills rounds of resident blocks best
+// the best one in the mean (1.0% where the keys stay in the cache).  The chunk that fills rounds of resident blocks best
 // was 7.0% off, whole chunks per CU with a fixed cost per block 3.3% (us, the
 // three in turn, fp8 keys: 16 sessions of 15K to 60K 19.4, 19.4, 25.8; 48 of 8192
 // with 2 tokens 19.1, 18.8, 23.8; 256 of 4000 32.0, 40.6, 32.0; one of 1M with 63

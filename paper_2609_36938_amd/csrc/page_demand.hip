@@ -13,12 +13,12 @@
 // emits a slice of RUN_THREADS words, one word per thread: what lies before
 // the slice (pages, run starts, the last unset page) it counts itself, so that
 // the slices need nothing from each other.
-// Few rows: one block does all of it, in one launch instead of three.
+// Few rows: one block does all of it, in one launch instead of three (pd_one_block).
 //
 // What bounds all of these is latency: chains of loads and barriers, and the
 // launches.  Measured: the union of 4096 rows of 2048 ids 28 -> 10 us, of 64
-// rows 20 -> 5; list and runs of 2.1K pages 5 -> 4.2, of 81K pages 12 -> 10.4;
-// two rows in one launch 7.6 us instead of 1 + 7 + 12 in three.
+// rows 20 -> 5; list and runs of 81K pages 12 -> 10.6; two rows in one launch 7.1
+// us instead of 1 + 7 + 12 in three.
 #include "janus_device.hpp"
 #include "janus_host.hpp"
 #include "launch_rules.hpp"

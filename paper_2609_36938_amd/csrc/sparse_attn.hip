@@ -943,8 +943,8 @@ __global__ __launch_bounds__(64 * NW, 1) void sparse_mla_mfma(
 // former).  With 128 heads the waves' own reads of K and V (each all of them)
 // would bound the kernel (1239 us against 1107): the kernel above shares V.
 // Measured at 2048 rows x 2048 ids of a 64K history, against one to four waves
-// per CU: 16 heads 1793 -> 410 us (11.8 TB/s of logical gather), 32 heads 1323
-// -> 501, 64 heads 1158 -> 679.
+// per CU: 16 heads 1793 -> 410 us (11.8 TB/s of logical gather, 4.2-4.7 of it past
+// L2 by the counters; MFMA busy 21%), 32 heads 1323 -> 501, 64 heads 1158 -> 679.
 //
 // Tile layout: dims 0..511 of row r (1 KB) at 1024 r, 16-byte chunk c at slot
 // c ^ few_swz(r): the 16 rows of a K operand read fall in 16 different

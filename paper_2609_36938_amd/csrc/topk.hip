@@ -32,9 +32,10 @@
 // 8-bit digits from the top took four (the first ones all but one bin wide,
 // their atomics serialised), register scans replace shuffles, and waves that
 // stream on their own need no barrier per stage.  Measured (k = 2048 unless
-// stated): 4096 rows of 135K 500 -> 400 us (5.5 TB/s), 64 rows of 32K-158K 55
-// -> 24, 512 shards of 16K (k = 256) 21 -> 13, one row of 13K 27 -> 15, 2048
-// rows of 8.2K (k = 512) 90 -> 50.
+// stated): 4096 rows of 135K 500 -> 397 us (5.6 TB/s of scores, 6.2 with the
+// sample; behind the prefill indexer 8192 rows of 139K take 870 us as before,
+// alone 992 -> 813), 64 rows of 32K-158K 55 -> 24, 512 shards of 16K (k = 256)
+// 21 -> 13, one row of 13K 27 -> 14, 2048 rows of 8.2K (k = 512) 90 -> 48.
 #include "janus_device.hpp"
 #include "janus_host.hpp"
 #include "launch_rules.hpp"

@@ -1082,21 +1082,21 @@ constexpr int ROWS_NQ = 4;
 // Block -> (session, first key), chunks of 2^shift keys, blocks numbered by
 // rows_first.  The wave looks for the session 64 ways a step: one step up to 64
 // sessions, two up to 4096 (a scan of the chunk counts took a step per 64
-// sessions: 4096 sessions of 1000 keys 288 us, now 145).  Scalar results.
-JANUS_DEV void rows_block(const int32_t *ctx_start, int num_seqs, int shift, int block, int &b, int &c0)
+// sessions: 4096 sessions of 1000 keys 288 us, now 114).  Scalar results; ks is
+// the session's first key row, ctx_start[b].
+JANUS_DEV void rows_block(const int32_t *ctx_start, int num_seqs, int shift, int block, int &b, int &c0, int &ks)
 {
     const int lane = threadIdx.x & 63;
-    b = 0;
-    int b_first = 0;
+    b = ks = 0;
     for (int n = num_seqs; n > 1;) {  // the session is one of b .. b + n - 1
         const int step = (n + kWave - 1) / kWave, s = b + min(lane * step, n - 1);
-        const int first = rows_first(ctx_start[s], s, shift);  // (by every lane: a load behind a branch cost registers)
-        const int l = __popcll(__ballot(lane * step < n && first <= block)) - 1;
+        const int start = ctx_start[s];  // (by every lane: a load behind a branch cost registers)
+        const int l = __popcll(__ballot(lane * step < n && rows_first(start, s, shift) <= block)) - 1;
         b += l * step;
-        b_first = __builtin_amdgcn_readlane(first, l);
+        ks = __builtin_amdgcn_readlane(start, l);
         n = min(step, n - l * step);
     }
-    c0 = (block - b_first) << shift;
+    c0 = (block - rows_first(ks, b, shift)) << shift;
 }
 
 template <int NQ, bool FP4>
@@ -1107,13 +1107,17 @@ __global__ __launch_bounds__(256, 2) void index_scores_rows(
     const uint8_t *__restrict__ k_bscale, const float *__restrict__ k_scale, const float *__restrict__ w,
     float *__restrict__ scores)
 {
+    // all arguments in one batch of loads: the compiler puts off those that an
+    // empty block does without, a round trip that every block waits for
+    asm volatile("" : : "s"(score_start), "s"(q), "s"(q_scale), "s"(kI), "s"(k_scale), "s"(w), "s"(scores));
     // per_seq blocks for each session, chunk fastest, or (0) numbered by rows_first
-    int b, c0;
+    int b, c0, ks;
     if (per_seq > 0) {
         b = blockIdx.x / per_seq;
         c0 = (blockIdx.x - b * per_seq) * chunk;
+        ks = ctx_start[b];
     } else {
-        rows_block(ctx_start, num_seqs, 31 - __builtin_clz(chunk), (int)blockIdx.x, b, c0);
+        rows_block(ctx_start, num_seqs, 31 - __builtin_clz(chunk), (int)blockIdx.x, b, c0, ks);
     }
     constexpr int t0 = 0;
     const int qs = q_start[b], N = q_start[b + 1] - qs;
@@ -1177,7 +1181,7 @@ __global__ __launch_bounds__(256, 2) void index_scores_rows(
     // the session's keys (block scales, key scales) from c0 on: rows past the
     // context read as zeros; its score rows (row t at t * ctx): stores past
     // them drop
-    const int64_t kbase = (int64_t)ctx_start[b] + c0;
+    const int64_t kbase = (int64_t)ks + c0;
     const __amdgpu_buffer_rsrc_t krs = make_buffer_rsrc((void *)(kI + kbase * KB), (uint32_t)(ctx - c0) * KB);
     const __amdgpu_buffer_rsrc_t bsr =
         make_buffer_rsrc((void *)(FP4 ? k_bscale + kbase * 4 : nullptr), FP4 ? (uint32_t)(ctx - c0) * 4u : 0u);

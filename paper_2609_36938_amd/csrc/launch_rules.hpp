@@ -84,23 +84,25 @@ constexpr int64_t ROWS_MAX_BLOCKS = (1 << 24) - 1;  // a launch takes fewer than
 // CU, by the blocks that the fullest CU takes (a session of C keys makes about
 // C / chunk + 1/2; one block more than the CUs is left out: the last key of a
 // power of two and one).  The first block costs its start and its keys.  Each
-// next one that is resident beside it (3 blocks a CU with one token per session,
-// else 2) runs mostly under it, but for what the memory takes for its keys; with
+// next one that is resident beside it (with one token per session 3 blocks a CU,
+// 4 with FP4 keys, else 2) runs mostly under it, but for what the memory takes for its keys; with
 // the CU full, the next one costs like the first.  The constants are fitted to
 // 1071 batches of 1 to 4096 sessions of 500 to 1M keys, even and ragged, with 1,
-// 2 and 4 tokens and both key types, keys from HBM: the chunk taken is 0.9% off
-// the best one in the mean (1.0% where the keys stay in the cache).  The chunk that fills rounds of resident blocks best
-// was 7.0% off, whole chunks per CU with a fixed cost per block 3.3% (us, the
-// three in turn, fp8 keys: 16 sessions of 15K to 60K 19.4, 19.4, 25.8; 48 of 8192
-// with 2 tokens 19.1, 18.8, 23.8; 256 of 4000 32.0, 40.6, 32.0; one of 1M with 63
-// of 1K and 2 tokens 42, 51, 42; 64 of 32K to 164K 151, 151, 150).
+// 2 and 4 tokens and both key types: the chunk taken is 0.9% off the best one in
+// the mean with keys from HBM and 1.3% with keys in the cache.  The chunk that
+// fills rounds of resident blocks best was 7.3% and 10% off, whole chunks per CU
+// with a fixed cost per block 3.3% and 4.2% (us, the three in turn, fp8 keys: 16
+// sessions of 15K to 60K 19.4, 19.4, 25.8; 48 of 8192 with 2 tokens 19.1, 18.8,
+// 23.8; 256 of 4000 32.0, 40.6, 32.0; one of 1M with 63 of 1K and 2 tokens 42, 51,
+// 42; 64 of 32K to 164K 151, 151, 150).
 // Blocks are numbered by rows_first unless the grid of the longest session's
 // chunks for each session needs no more of them, or has each on a CU of its own:
 // it saves the search, 0.2 us.
 constexpr RowsPlan rows_plan(int num_seqs, int max_ctx, int64_t total_ctx, int max_q, int cus, bool fp4)
 {
     const bool one = max_q <= 1;
-    const int resident = one ? 3 : 2, start = fp4 ? 384 : 128, beside = fp4 ? 256 : one ? 448 : 1024;
+    const int resident = one ? fp4 ? 4 : 3 : 2;
+    const int start = fp4 ? one ? 512 : 384 : 128, beside = fp4 ? one ? 384 : 256 : one ? 448 : 1024;
     RowsPlan best = {0, 0, 0};
     double best_cost = -1.0;
     for (int c = one ? 2048 : 4096; c >= ROWS_CHUNK_MIN; c /= 2) {
